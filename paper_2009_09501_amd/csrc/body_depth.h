@@ -68,21 +68,6 @@ __device__ __forceinline__ uint32_t block_mean(uint32_t sum, uint32_t cnt) {
     return (sum + cnt / 2) / cnt;
 }
 
-// The n (1..4) pixels of a quad starting at p as three dwords of RGB24 bytes,
-// zero past the n-th pixel.  ALIGNED: a whole quad at a 4-byte aligned address.
-template <bool ALIGNED>
-__device__ __forceinline__ uint3 load_quad_words(const uint8_t* p, int n) {
-    if constexpr (ALIGNED) {
-        return *reinterpret_cast<const uint3*>(p);
-    } else {
-        uint32_t w[3] = {0u, 0u, 0u};
-#pragma unroll
-        for (int i = 0; i < 12; ++i)
-            if (i < 3 * n) w[i >> 2] |= (uint32_t)p[i] << (8 * (i & 3));
-        return make_uint3(w[0], w[1], w[2]);
-    }
-}
-
 // Luma of the four pixels of a quad held in three dwords.
 __device__ __forceinline__ void bs_quad_luma(uint3 q, uint32_t (&Y)[4]) {
     constexpr uint32_t wlo = 77u | (150u << 8) | (29u << 16);

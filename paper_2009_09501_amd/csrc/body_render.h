@@ -3,8 +3,8 @@
 //
 //   k_cbf   pixel depth (from the block tables) and its cross-bilateral
 //           filter guided by luma (Section 3: filtered depth map; Section 4:
-//           GPU cross-bilateral filtering), on 64 x 16 pixel tiles with a
-//           halo in LDS.  Windows whose depths are all equal take the exact
+//           GPU cross-bilateral filtering), on 64 x 32 or 64 x 16 pixel
+//           tiles with a halo in LDS.  Windows whose depths are all equal take the exact
 //           shortcut; the other quads are compacted into a workgroup list so
 //           that only they pay for the weighted sum.  Output: filtered depth,
 //           one byte per pixel, in a scratch buffer.
@@ -618,20 +618,7 @@ __device__ __forceinline__ void store_quad_views(const FrameDesc& f, int y, int 
     const int W = f.w;
     const int n = min(4, W - x0);
     const size_t off = ((size_t)y * W + x0) * 3;
-    // unaligned rows: byte stores of the quad's pixels inside the row
-    auto store4 = [&](uint8_t* out, uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3) {
-        if (!out) return;
-        const uint32_t c[4] = {c0, c1, c2, c3};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (j < n) {
-                out[off + 3 * j] = (uint8_t)c[j];
-                out[off + 3 * j + 1] = (uint8_t)(c[j] >> 8);
-                out[off + 3 * j + 2] = (uint8_t)(c[j] >> 16);
-            }
-        }
-    };
-    if (ALIGNED) {
+    if (ALIGNED || n == 4) {
         // both views packed once; in the three dwords of a quad the red bytes
         // sit at fixed places, so the anaglyph is one bit-field insert per
         // dword
@@ -639,18 +626,26 @@ __device__ __forceinline__ void store_quad_views(const FrameDesc& f, int y, int 
                                     perm(cl[3], cl[2], 0x06050402u));
         const uint3 rp = make_uint3(perm(cr[1], cr[0], 0x04020100u), perm(cr[2], cr[1], 0x05040201u),
                                     perm(cr[3], cr[2], 0x06050402u));
-        if (f.out_l) *reinterpret_cast<uint3*>(f.out_l + off) = lp;
-        if (f.out_r) *reinterpret_cast<uint3*>(f.out_r + off) = rp;
+        auto store3 = [&](uint8_t* out, uint3 v) {
+            if (ALIGNED) *reinterpret_cast<uint3*>(out + off) = v;
+            else store_96(out + off, v);
+        };
+        if (f.out_l) store3(f.out_l, lp);
+        if (f.out_r) store3(f.out_r, rp);
         if (f.out_a) {
             constexpr uint32_t m0 = 0xFF0000FFu, m1 = 0x00FF0000u, m2 = 0x0000FF00u;
-            *reinterpret_cast<uint3*>(f.out_a + off) =
-                make_uint3((lp.x & m0) | (rp.x & ~m0), (lp.y & m1) | (rp.y & ~m1), (lp.z & m2) | (rp.z & ~m2));
+            store3(f.out_a,
+                   make_uint3((lp.x & m0) | (rp.x & ~m0), (lp.y & m1) | (rp.y & ~m1), (lp.z & m2) | (rp.z & ~m2)));
         }
     } else {
-        store4(f.out_l, cl[0], cl[1], cl[2], cl[3]);
-        store4(f.out_r, cr[0], cr[1], cr[2], cr[3]);
-        store4(f.out_a, (cl[0] & 0xFFu) | (cr[0] & 0xFFFF00u), (cl[1] & 0xFFu) | (cr[1] & 0xFFFF00u),
-               (cl[2] & 0xFFu) | (cr[2] & 0xFFFF00u), (cl[3] & 0xFFu) | (cr[3] & 0xFFFF00u));
+        // the quad a row of another width ends with: byte stores of its pixels
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            if (j >= n) break;
+            if (f.out_l) store_px_bytes(f.out_l + off + 3 * j, cl[j]);
+            if (f.out_r) store_px_bytes(f.out_r + off + 3 * j, cr[j]);
+            if (f.out_a) store_px_bytes(f.out_a + off + 3 * j, (cl[j] & 0xFFu) | (cr[j] & 0xFFFF00u));
+        }
     }
     if (f.out_h) {
         const int hw = W >> 1;
@@ -688,11 +683,10 @@ __host__ __device__ constexpr size_t warp_lds_bytes(int w, int threads, int q) {
 }
 
 // A lane's share of one image row: the frame bytes of its Q quads (three
-// raw dwords per quad when aligned, else four decoded R | G << 8 | B << 16
-// colours) and their filtered depths.
+// raw dwords per quad) and their filtered depths.
 template <bool ALIGNED, int Q>
 struct WarpRowIn {
-    static constexpr int kPerQuad = ALIGNED ? 3 : 4;
+    static constexpr int kPerQuad = 3;
     uint32_t c[kPerQuad * Q];
     uint32_t dq[Q];
 };
@@ -712,21 +706,11 @@ __device__ __forceinline__ void warp_load(const FrameDesc& f, int y, int t, int 
         for (int j = 0; j < P; ++j) in.c[P * qi + j] = 0;
         in.dq[qi] = 0;
         if (x0 >= W) continue;
-        if (ALIGNED) {
-            const uint3 v = *reinterpret_cast<const uint3*>(q0 + (size_t)qi * 12 * NT);
-            in.c[P * qi] = v.x;
-            in.c[P * qi + 1] = v.y;
-            in.c[P * qi + 2] = v.z;
-            in.dq[qi] = *reinterpret_cast<const uint32_t*>(drow + x0);
-        } else {
-            const int n = min(4, W - x0);
-            const uint8_t* p = f.frame + ((size_t)y * W + x0) * 3;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                in.c[P * qi + j] = j < n ? (p[3 * j] | ((uint32_t)p[3 * j + 1] << 8) | ((uint32_t)p[3 * j + 2] << 16)) : 0u;
-                if (j < n) in.dq[qi] |= (uint32_t)drow[x0 + j] << (8 * j);
-            }
-        }
+        const uint3 v = load_quad_words<ALIGNED>(q0 + (size_t)qi * 12 * NT, W - x0);
+        in.c[P * qi] = v.x;
+        in.c[P * qi + 1] = v.y;
+        in.c[P * qi + 2] = v.z;
+        in.dq[qi] = load_quad_bytes<ALIGNED>(drow + x0, W - x0);
     }
 }
 
@@ -881,12 +865,7 @@ __device__ __forceinline__ void warp_row_body(const FrameDesc& f, int y, int t, 
         if (x0 >= W) continue;
         const int n = ALIGNED ? 4 : min(4, W - x0);
         uint32_t c[4];
-        if (ALIGNED) {
-            quad_colours(make_uint3(in.c[3 * qi], in.c[3 * qi + 1], in.c[3 * qi + 2]), c);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) c[j] = in.c[4 * qi + j];
-        }
+        quad_colours(make_uint3(in.c[3 * qi], in.c[3 * qi + 1], in.c[3 * qi + 2]), c);
         const uint32_t dq = in.dq[qi];
         *reinterpret_cast<uint32_t*>(drow_l + x0) = dq;
 #pragma unroll
@@ -1077,29 +1056,14 @@ __device__ __forceinline__ void gather_row(const FrameDesc& f, int y, int t, int
     const uint8_t* src = f.frame + (size_t)y * W * 3;
     for (int x0 = 4 * t; x0 < W; x0 += 4 * NT) {
         uint32_t c[4];
-        if (ALIGNED) {
-            quad_colours(*reinterpret_cast<const uint3*>(src + (size_t)x0 * 3), c);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint8_t* p = src + (size_t)(x0 + j) * 3;
-                c[j] = x0 + j < W ? (p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16)) : 0u;
-            }
-        }
+        quad_colours(load_quad_words<ALIGNED>(src + (size_t)x0 * 3, W - x0), c);
 #pragma unroll
         for (int j = 0; j < 4; ++j) rowc[kidx(x0 + j)] = c[j];
     }
     __syncthreads();
     const uint8_t* drow = f.df + (size_t)y * W;
     for (int x0 = 4 * t; x0 < W; x0 += 4 * NT) {
-        uint32_t dq = 0;
-        if (ALIGNED) {
-            dq = *reinterpret_cast<const uint32_t*>(drow + x0);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (x0 + j < W) dq |= (uint32_t)drow[x0 + j] << (8 * j);
-        }
+        const uint32_t dq = load_quad_bytes<ALIGNED>(drow + x0, W - x0);
         uint32_t cl[4], cr[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {

@@ -50,23 +50,72 @@ __device__ __forceinline__ int ramp(int row, int gh) {
 
 __device__ __forceinline__ int iabs(int v) { return v < 0 ? -v : v; }
 
-// Four RGB24 pixels starting at p.  ALIGNED: the frame width is divisible by 4
-// and the buffer is 4-byte aligned, so p is 4-byte aligned and all four pixels
-// exist; otherwise n (0..4) pixels exist and are read bytewise.
+// Loads and stores of dwords at any byte address: the hardware takes
+// unaligned global accesses, and the compiler forms one instruction for each.
+struct __attribute__((packed)) Bytes12 { uint32_t x, y, z; };
+
+__device__ __forceinline__ uint3 load_96(const uint8_t* p) {
+    Bytes12 v;
+    __builtin_memcpy(&v, p, 12);
+    return make_uint3(v.x, v.y, v.z);
+}
+__device__ __forceinline__ void store_96(uint8_t* p, uint3 q) {
+    const Bytes12 v = {q.x, q.y, q.z};
+    __builtin_memcpy(p, &v, 12);
+}
+__device__ __forceinline__ uint32_t load_32(const uint8_t* p) {
+    uint32_t v;
+    __builtin_memcpy(&v, p, 4);
+    return v;
+}
+__device__ __forceinline__ void store_32(uint8_t* p, uint32_t v) { __builtin_memcpy(p, &v, 4); }
+
+// The n (1..4) pixels of a quad starting at p as three dwords of RGB24 bytes,
+// zero past the n-th pixel.  ALIGNED: a whole quad at a 4-byte aligned
+// address; otherwise a whole quad is one load too, and the quad a row of
+// another width ends with (n < 4) is read bytewise.
 template <bool ALIGNED>
-__device__ __forceinline__ void load_quad(const uint8_t* p, int n, int (&r)[4], int (&g)[4], int (&b)[4]) {
+__device__ __forceinline__ uint3 load_quad_words(const uint8_t* p, int n) {
     if constexpr (ALIGNED) {
-        const uint3 v = *reinterpret_cast<const uint3*>(p);
-        r[0] = v.x & 255;         g[0] = (v.x >> 8) & 255;  b[0] = (v.x >> 16) & 255;
-        r[1] = v.x >> 24;         g[1] = v.y & 255;         b[1] = (v.y >> 8) & 255;
-        r[2] = (v.y >> 16) & 255; g[2] = v.y >> 24;         b[2] = v.z & 255;
-        r[3] = (v.z >> 8) & 255;  g[3] = (v.z >> 16) & 255; b[3] = v.z >> 24;
+        return *reinterpret_cast<const uint3*>(p);
     } else {
+        if (n >= 4) return load_96(p);
+        uint32_t w[3] = {0u, 0u, 0u};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (j < n) { r[j] = p[3 * j]; g[j] = p[3 * j + 1]; b[j] = p[3 * j + 2]; }
-            else { r[j] = g[j] = b[j] = 0; }
+        for (int i = 0; i < 9; ++i)
+            if (i < 3 * n) w[i >> 2] |= (uint32_t)p[i] << (8 * (i & 3));
+        return make_uint3(w[0], w[1], w[2]);
+    }
+}
+
+// The n (1..4) bytes at p, zero past the n-th; the same rule.
+template <bool ALIGNED>
+__device__ __forceinline__ uint32_t load_quad_bytes(const uint8_t* p, int n) {
+    if constexpr (ALIGNED) {
+        return *reinterpret_cast<const uint32_t*>(p);
+    } else {
+        if (n >= 4) return load_32(p);
+        uint32_t w = 0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (i < n) w |= (uint32_t)p[i] << (8 * i);
+        return w;
+    }
+}
+
+// The low n (1..4) bytes of v to p; the same rule.
+template <bool ALIGNED>
+__device__ __forceinline__ void store_quad_bytes(uint8_t* p, uint32_t v, int n) {
+    if constexpr (ALIGNED) {
+        *reinterpret_cast<uint32_t*>(p) = v;
+    } else {
+        if (n >= 4) {
+            store_32(p, v);
+            return;
         }
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (i < n) p[i] = (uint8_t)(v >> (8 * i));
     }
 }
 

@@ -1,0 +1,46 @@
+"""GPU tests of the kernels at the sizes where their variants meet: rows that
+do not start on a dword.  Every output is compared with the oracle byte for
+byte."""
+import pytest
+
+import refs
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+_GUARD = 0xA5
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2009_09501_amd import Context
+    c = Context(0, 7680, 4320)
+    yield c
+    c.close()
+
+
+@pytest.mark.parametrize("w,h,off", [(1, 3, 0), (2, 2, 1), (3, 5, 2), (6, 4, 3), (255, 9, 0), (257, 34, 1),
+                                     (258, 33, 2), (259, 70, 3), (1366, 130, 0), (2049, 8, 0), (4102, 6, 1)])
+def test_rows_off_the_dword_grid(ctx, w, h, off):
+    """Widths that are no multiple of 4 and buffers at any byte offset: whole
+    quads go as unaligned dwords, a row's last 1 to 3 pixels as bytes, and no
+    byte beside an output is written."""
+    from paper_2009_09501_amd import pstereo_params_init, pstereo_synthesize
+    dev = torch.device("cuda:0")
+    host = synth.gen_frame(900 + w + off, w, h, 10, 4.0)
+    n = 3 * w * h
+    src = torch.zeros(n + 16, dtype=torch.uint8, device=dev)
+    src[off:off + n] = torch.from_numpy(host.reshape(-1)).to(dev)
+    bufs = [torch.full((n + 16,), _GUARD, dtype=torch.uint8, device=dev) for _ in range(3)]
+    B = min(12, w)
+    p = pstereo_params_init(max_disparity=B)
+    p.stream = torch.cuda.current_stream().cuda_stream
+    print(f"off the grid: {w}x{h} at byte offset {off}", flush=True)
+    pstereo_synthesize(ctx.handle, src[off:], w, h, p, *[b[off:] for b in bufs])
+    torch.cuda.synchronize()
+    want = refs.views(("edges", w, h, off), host, B)
+    refs.assert_views([b[off:off + n].cpu().view(h, w, 3) for b in bufs], want, f"{w}x{h} offset {off}")
+    for b in bufs:
+        assert bool((b[:off] == _GUARD).all()) and bool((b[off + n:] == _GUARD).all()), "bytes beside an output written"
