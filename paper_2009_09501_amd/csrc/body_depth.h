@@ -606,7 +606,7 @@ __device__ __forceinline__ void regions_body(const FrameDesc& f, uint32_t* lds) 
         const int b = i * kRegionThreads + t;
         if (b < nb) {
             const uint32_t v = parent[pidx(b)];
-            binfo_w[2 * b + 1] = v & 255u;
+            binfo_w[2 * b + 1] = (v & 255u) | kResolved;
             f.labels[b] = (int32_t)(v >> 8);
         }
     }

@@ -116,12 +116,13 @@ __device__ __forceinline__ void quad_luma2(uint3 v, uint32_t& y01, uint32_t& y23
     y23 = perm(r3, r2, 0x0c050c01u) << 1;
 }
 
-// Region depth of a block in row by after the strip-parallel grouping, from
-// its {statistics, component slot}: edge blocks and the background follow
+// Region depth of a block in row by from its {statistics, region} entry: the
+// entry holds the depth itself (kResolved) after the single-workgroup
+// grouping, else its component's slot; edge blocks and the background follow
 // the row ramp, other blocks take their merged component's depth.
-__device__ __forceinline__ uint32_t block_depth_from_slots(const FrameDesc& f, int by, uint2 e) {
-    if (e.x >> 24) return (uint32_t)ramp(by, f.gh);
-    const uint32_t v = f.rfin[e.y];
+__device__ __forceinline__ uint32_t block_depth(const FrameDesc& f, int by, uint2 e) {
+    if (e.y & kResolved) return e.y & 255u;
+    const uint32_t v = (e.x >> 24) ? 256u : f.rfin[e.y];
     return ((v >> 8) & 1u) ? (uint32_t)ramp(by, f.gh) : (v & 255u);
 }
 
@@ -138,13 +139,14 @@ constexpr uint32_t kNoCandidate = 0xFC000000u;
 // the ramp of the block row.  col[j] = R | G << 8 | B << 16 of pixel j; the
 // L1 distance to a block mean (stats word, edge byte zero for candidates) is
 // one v_sad_u8.  The blocks come from a table staged in LDS: tab holds the
-// blocks [bx_lo, bx_lo + bw) x [by_lo, ...), {statistics, search key}, and
-// covers every in-grid block the lookup can touch; K = 1 << ks.
+// blocks from (bx_lo, by_lo) on, bp entries a row, {statistics, search key},
+// and covers every block the lookup can touch; K = 1 << ks.
 __device__ __forceinline__ void quad_depth_tab(const FrameDesc& f, int x0, int yy, int ks, const uint2* tab,
-                                               int bx_lo, int by_lo, int bw, const uint32_t (&col)[4],
+                                               int bx_lo, int by_lo, int bp, const uint32_t (&col)[4],
                                                uint32_t (&D)[4]) {
-    const int bx = x0 >> ks, by = yy >> ks;
-    const uint2 own = tab[(by - by_lo) * bw + (bx - bx_lo)];
+    const int by = yy >> ks;
+    const uint2* at = tab + (__umul24(by - by_lo, bp) + ((x0 >> ks) - bx_lo));
+    const uint2 own = *at;
     if (!(own.x >> 24)) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) D[j] = own.y;
@@ -157,7 +159,7 @@ __device__ __forceinline__ void quad_depth_tab(const FrameDesc& f, int x0, int y
     uint32_t best[4] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
-        const uint2 c = tab[(by - by_lo + k / 3 - 1) * bw + (bx - bx_lo + k % 3 - 1)];
+        const uint2 c = at[(k / 3 - 1) * bp + (k % 3 - 1)];
         const uint32_t tag = c.y | ((uint32_t)k << 8);
 #pragma unroll
         for (int j = 0; j < 4; ++j) best[j] = min(best[j], __builtin_amdgcn_sad_hi_u8(col[j], c.x, tag));
@@ -175,22 +177,21 @@ __device__ __forceinline__ void quad_depth_tab(const FrameDesc& f, int x0, int y
 // Raw depth of the four pixels of a quad for blocks of 2 px (the quad spans
 // two block columns): the same rule as quad_depth_tab, per pixel, from the
 // block table in global memory (frames of 2 px blocks hold at most 2^17
-// pixels, so this path is never the bulk of the work).  strips: block depths
-// are resolved through the merge's slot table.
-__device__ __forceinline__ uint2 block_entry_global(const FrameDesc& f, int bx, int by, bool strips) {
+// pixels, so this path is never the bulk of the work).
+__device__ __forceinline__ uint2 block_entry_global(const FrameDesc& f, int bx, int by) {
     if (bx < 0 || bx >= f.gw || by < 0 || by >= f.gh) return make_uint2(1u << 24, 0u);
     uint2 e = f.binfo[by * f.gw + bx];
-    if (strips) e.y = block_depth_from_slots(f, by, e);
+    e.y = block_depth(f, by, e);
     return e;
 }
 
-__device__ __forceinline__ void quad_depth_k2(const FrameDesc& f, int x0, int yy, bool strips,
-                                              const uint32_t (&col)[4], uint32_t (&D)[4]) {
+__device__ __forceinline__ void quad_depth_k2(const FrameDesc& f, int x0, int yy, const uint32_t (&col)[4],
+                                              uint32_t (&D)[4]) {
     const int by = yy >> 1;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int bx = (x0 + j) >> 1;
-        const uint2 own = block_entry_global(f, bx, by, strips);
+        const uint2 own = block_entry_global(f, bx, by);
         if (!(own.x >> 24)) {
             D[j] = own.y;
             continue;
@@ -200,7 +201,7 @@ __device__ __forceinline__ void quad_depth_k2(const FrameDesc& f, int x0, int yy
         int best = -1;
         uint32_t bestd = 0, bestdep = 0;
         for (int k = 0; k < 9; ++k) {
-            const uint2 c = block_entry_global(f, bx + k % 3 - 1, by + k / 3 - 1, strips);
+            const uint2 c = block_entry_global(f, bx + k % 3 - 1, by + k / 3 - 1);
             if (c.x >> 24) continue;
             const uint32_t d = __builtin_amdgcn_sad_u8(col[j], c.x, 0u);
             if (best < 0 || d < bestd) {
@@ -214,13 +215,24 @@ __device__ __forceinline__ void quad_depth_k2(const FrameDesc& f, int x0, int yy
 }
 
 // ---------------------------------------------------------------------------
-// k_cbf: 64 x 32 pixel tiles, 256 lanes; lane = one quad in each of two tile
-// rows (ty and ty + 16).  LDS holds, for the tile and a 4 px / R row halo,
-// doubled luma and raw depth as u16 pairs (two dwords per quad).  A window of
-// quad x0 reads the six dwords of columns x0-4 .. x0+7 per row.
+// k_cbf: 64 x TH pixel tiles (TH = 32, or 16 for small frames), 256 lanes;
+// lane = one quad in every 16th tile row.  LDS holds, for the tile and a
+// 4 px / R row halo, doubled luma and raw depth as u16 pairs (two dwords per
+// quad).  A window of quad x0 reads the six dwords of columns x0-4 .. x0+7 per
+// row.
+//
+// Bound: small frames, the serial chain of one workgroup (staging, luma and
+// depth, window tests, filter); 4K and up, VALU issue (7.9 M wave
+// instructions a 4K frame, 13 us of the 23.5) plus the last round's tail.
+// With the taps free of image-bounds tests, the block table loaded first, the
+// slot flag in the entry instead of a control word (whose load waited for the
+// whole frame tile) and 32-bit offsets: 640x360 13.2 -> 7.2 us, 1920x1080 14.5
+// -> 11.7, 1920x1080 of an external depth map at R = 3 31.5 -> 20.3, 3840x2160
+// 25.5 -> 23.5, 7680x4320 64.7 -> 58.5.  512 lanes per 32-row tile (twice the
+// waves, each with its own set-up) took 27.7 us at 4K.
 constexpr int kTileQ = 16;                   // quads per tile row
 constexpr int kTileW = 4 * kTileQ;           // 64 px
-constexpr int kTileH = 32;                   // rows
+constexpr int kTileH = 32;                   // rows (default)
 constexpr int kTileQuads = kTileQ + 2;       // quads per LDS row: one extra each side
 constexpr int kRowWords = 2 * kTileQuads;    // 36 dwords per LDS row and plane
 
@@ -232,45 +244,49 @@ struct CbfPairWin {
     static constexpr int kWords = (2 * kW0 + 1 + R) / 2 + 1;
 };
 
-// Filtered depth of the two pixels x0, x0 + 1 of one row.  yw / dw: the
-// window words of each of the 2R + 1 rows, luma doubled and raw depth as u16
-// pairs; pixel j sits at window column 2 kW0 + j, so every tap's word and half
-// are compile-time constants.  Taps go in pairs (c, c + 1) of one word (c
-// even; a pair's tap outside dx = -R..R has weight 0 and reads nothing), so
-// the weighted depth sum and the weight sum each take one dot2 per pair on the
-// word as stored.  CLIP: some window column lies outside the image and gets
-// weight 0.
-template <int R, bool CLIP>
+// Doubled luma of a pixel outside the image: kRangeTaps above the largest
+// luma, so its difference from every guide pixel has range weight 0 and the
+// pixel drops out of both sums with no test (its entries run up to 42 past a
+// table row: the zero head of the next row, or the table's zero tail).
+constexpr uint32_t kLumaOut = 2u * (255 + kRangeTaps);
+constexpr int kWtabTail = 32;  // words of zeros after the table's last row
+static_assert(kLumaOut / 2 + 255 < 512 + 2 * kWtabTail, "outside pixels read zeros");
+
+// Filtered depth of the two pixels of a pair.  yw / dw: the window words of
+// each of the 2R + 1 rows, luma doubled and raw depth as u16 pairs; pixel j
+// sits at window column 2 kW0 + j, so every tap's word and half are
+// compile-time constants.  Taps go in pairs (c, c + 1) of one word (c even; a
+// pair's tap outside dx = -R..R has weight 0 and reads nothing), so the
+// weighted depth sum and the weight sum each take one dot2 per pair on the
+// word as stored.  Straight-line: pixels outside the image carry kLumaOut
+// (weight 0), so no tap is tested and all table reads can be in flight.
+template <int R>
 __device__ __forceinline__ void cbf_pair(const uint32_t (&yw)[2 * R + 1][CbfPairWin<R>::kWords],
-                                         const uint32_t (&dw)[2 * R + 1][CbfPairWin<R>::kWords], uint32_t rows_ok,
-                                         int x0, int W, const uint16_t* wtab, uint32_t (&df)[2]) {
+                                         const uint32_t (&dw)[2 * R + 1][CbfPairWin<R>::kWords],
+                                         const uint16_t* wtab, uint32_t (&df)[2]) {
     constexpr int PW = CbfPairWin<R>::kWords;
     const uint8_t* wt = reinterpret_cast<const uint8_t*>(wtab);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
         const int pc = 2 * CbfPairWin<R>::kW0 + j;
         // byte offset of a tap's weight in its table row: 2 Yq + (510 - 2 Yp)
-        const uint32_t base = 510u - ((yw[R][pc >> 1] >> (16 * (pc & 1))) & 0xFFFFu);
+        // (a pixel past the row's end, never stored, counts as luma 255)
+        const uint32_t base = 510u - min((yw[R][pc >> 1] >> (16 * (pc & 1))) & 0xFFFFu, 510u);
         uint32_t acc = 0, wsum = 0;
 #pragma unroll
         for (int dy = -R; dy <= R; ++dy) {
-            if (!((rows_ok >> (dy + R)) & 1u)) continue;
             const uint32_t(&yr)[PW] = yw[dy + R];
             const uint32_t(&dr)[PW] = dw[dy + R];
 #pragma unroll
             for (int dx = -R - ((pc - R) & 1); dx <= R; dx += 2) {
                 const int c = pc + dx;  // even
                 uint32_t w0 = 0, w1 = 0;
-                if (dx >= -R) {
-                    const uint32_t y0 = yr[c >> 1] & 0xFFFFu;
-                    w0 = *reinterpret_cast<const uint16_t*>(wt + k_index(dx * dx + dy * dy) * 1024 + (y0 + base));
-                    if (CLIP && (unsigned)(x0 + j + dx) >= (unsigned)W) w0 = 0;
-                }
-                if (dx + 1 <= R) {
-                    const uint32_t y1 = yr[c >> 1] >> 16;
-                    w1 = *reinterpret_cast<const uint16_t*>(wt + k_index((dx + 1) * (dx + 1) + dy * dy) * 1024 + (y1 + base));
-                    if (CLIP && (unsigned)(x0 + j + dx + 1) >= (unsigned)W) w1 = 0;
-                }
+                if (dx >= -R)
+                    w0 = *reinterpret_cast<const uint16_t*>(wt + k_index(dx * dx + dy * dy) * 1024 +
+                                                            ((yr[c >> 1] & 0xFFFFu) + base));
+                if (dx + 1 <= R)
+                    w1 = *reinterpret_cast<const uint16_t*>(wt + k_index((dx + 1) * (dx + 1) + dy * dy) * 1024 +
+                                                            ((yr[c >> 1] >> 16) + base));
                 const uint32_t wp = w0 | (w1 << 16);
                 acc = dot2_u16(wp, dr[c >> 1], acc);
                 wsum = dot2_u16(wp, 0x00010001u, wsum);
@@ -280,71 +296,108 @@ __device__ __forceinline__ void cbf_pair(const uint32_t (&yw)[2 * R + 1][CbfPair
     }
 }
 
-template <int R>
+// A tile of 64 x TH px (TH a multiple of 16) on 256 lanes.
+template <int R, int TH = kTileH>
 struct CbfTile {
-    static constexpr int TR = kTileH + 2 * R;  // LDS rows incl. halo
+    static constexpr int NT = 256;
+    static_assert(16 * TH % NT == 0, "whole passes over the tile's quads");
+    static constexpr int TR = TH + 2 * R;  // LDS rows incl. halo
     static constexpr int NK = k_count(R);
-    // tY, tD: TR * kRowWords words each; wtab: NK * 512 u16; work: 512 u16; nwork
-    // block table of the tile, its halo and one ring of neighbours: at most
-    // 21 x 13 blocks (K = 4, R = 3), uint2 each
-    static constexpr int kBlkEntries = 288;
-    static constexpr int kBlkOff = (2 * TR * kRowWords + NK * 256 + 256 + 1 + 1) & ~1;  // 8-byte aligned
+    // tY, tD: TR * kRowWords words each; wtab: NK * 512 u16 and its zero tail;
+    // work: 16 TH u16; nwork
+    // block table of the tile, its halo and one ring of neighbours, uint2
+    // each: at most 12 blocks a row (16 entries, TH / 8 + 4 rows) for blocks
+    // of 8 px and more, 20 x (TH / 4 + 4) for 4 px
+    static constexpr int kBlkEntries = 20 * (TH / 4 + 4);
+    static constexpr int kTabOff = 2 * TR * kRowWords;
+    static constexpr int kWorkOff = kTabOff + NK * 256 + kWtabTail;
+    static constexpr int kBlkOff = (kWorkOff + 8 * TH + 1 + 1) & ~1;  // 8-byte aligned
     static constexpr int kLdsWords = kBlkOff + 2 * kBlkEntries;
+    static constexpr int NQ = (TR * kTileQuads + NT - 1) / NT;  // quads per lane incl. halo
 };
 
-// A lane's frame loads for one tile: three raw dwords per quad of the tile
-// and its halo (aligned frames; unaligned ones load bytes in the prologue).
-template <int R>
-struct CbfIn {
-    static constexpr int NQ = (CbfTile<R>::TR * kTileQuads + 255) / 256;
-    uint3 vq[NQ];
-};
-
-// Issue the loads of tile (tile_x, tile_y) for lane t; quads outside the
-// image (or all, when H = 0) load nothing and are not read later.
-template <int R, bool ALIGNED>
-__device__ __forceinline__ void cbf_load(const FrameDesc& f, int tile_x, int tile_y, int t, int H, CbfIn<R>& in) {
-    if (!ALIGNED) return;
-    const int W = f.w, tx0 = tile_x * kTileW, ty0 = tile_y * kTileH;
-#pragma unroll
-    for (int k = 0; k < CbfIn<R>::NQ; ++k) {
-        const int i = t + 256 * k;
-        const int tr = i / kTileQuads, tq = i - tr * kTileQuads;
-        const int yy = ty0 - R + tr, x0 = tx0 - 4 + 4 * tq;
-        if (i < CbfTile<R>::TR * kTileQuads && yy >= 0 && yy < H && x0 >= 0 && x0 < W)
-            in.vq[k] = *reinterpret_cast<const uint3*>(f.frame + ((size_t)yy * W + x0) * 3);
-    }
-}
-
-// One 64 x 32 tile (tile_x, tile_y) on 256 lanes t = 0..255 (four whole
-// waves).  lds: CbfTile<R>::kLdsWords words.  Inactive lane groups do no
+// One 64 x TH tile (tile_x, tile_y) on 256 lanes t = 0..255 (four whole
+// waves).  lds: CbfTile<R, TH>::kLdsWords words.  Inactive lane groups do no
 // memory work but pass the same three barriers.  K2: blocks of 2 px (raw
 // depth looked up per pixel in global memory, no block table in LDS).
-template <int R, bool ALIGNED, bool K2 = false>
+template <int R, bool ALIGNED, bool K2 = false, int TH = kTileH>
 __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int tile_y, int t, uint32_t* lds,
                                          bool active) {
     constexpr int S = 2 * R + 1;
-    constexpr int TR = CbfTile<R>::TR;
-    constexpr int NK = CbfTile<R>::NK;
+    using T = CbfTile<R, TH>;
+    constexpr int NT = T::NT;
+    constexpr int TR = T::TR;
+    constexpr int NK = T::NK;
     uint32_t* tY = lds;
     uint32_t* tD = tY + TR * kRowWords;
-    uint16_t* wtab = reinterpret_cast<uint16_t*>(tD + TR * kRowWords);
-    uint16_t* work = wtab + NK * 512;
-    int* nwork_p = reinterpret_cast<int*>(work + 512);
+    uint16_t* wtab = reinterpret_cast<uint16_t*>(lds + T::kTabOff);
+    uint16_t* work = reinterpret_cast<uint16_t*>(lds + T::kWorkOff);
+    int* nwork_p = reinterpret_cast<int*>(work + 16 * TH);
     int& nwork = *nwork_p;
-    uint2* btab = reinterpret_cast<uint2*>(lds + CbfTile<R>::kBlkOff);
+    uint2* btab = reinterpret_cast<uint2*>(lds + T::kBlkOff);
 
     const int W = f.w, H = active ? f.h : 0;
-    const int tx0 = tile_x * kTileW, ty0 = tile_y * kTileH;
+    const int tx0 = tile_x * kTileW, ty0 = tile_y * TH;
 
-    // the frame loads of all of a lane's quads of the tile and its halo go
-    // out first, to arrive while the block table is staged
-    constexpr int NQ = CbfIn<R>::NQ;
-    CbfIn<R> in;
-    cbf_load<R, ALIGNED>(f, tile_x, tile_y, t, H, in);
+    // the tile's block table: its blocks, those of the halo and one ring of
+    // neighbours (clipped to the grid plus one ring outside it, whose entries
+    // are marked as edge blocks), bp entries a row.  A lane's first entry is
+    // loaded before anything else, so that the slot it leads to can be looked
+    // up while the frame arrives
+    const int ks = __builtin_ctz((unsigned)f.K);
+    const int bx_lo = max(-1, ((tx0 - 4) >> ks) - 1), bx_hi = min(f.gw, ((tx0 + 4 * kTileQuads - 5) >> ks) + 1);
+    const int by_lo = max(-1, ((ty0 - R) >> ks) - 1), by_hi = min(f.gh, ((ty0 + TH - 1 + R) >> ks) + 1);
+    const bool wide = ks >= 3;
+    const int bp = wide ? 16 : 20;
+    const int nbt = !K2 && !f.depth_in && H > 0 ? bp * (by_hi - by_lo + 1) : 0;
+    auto entry_pos = [&](int i, int& bx, int& by) {
+        const int r = wide ? i >> 4 : i / 20;
+        by = by_lo + r;
+        bx = bx_lo + (i - r * bp);
+    };
+    auto entry_load = [&](int bx, int by) {
+        uint2 e = make_uint2(1u << 24, kResolved);  // outside the grid: an edge block
+        if ((unsigned)by < (unsigned)f.gh && (unsigned)bx < (unsigned)f.gw && bx <= bx_hi)
+            e = f.binfo[__umul24(by, f.gw) + bx];
+        return e;
+    };
+    auto entry_store = [&](int i, int by, uint2 e) {
+        // an edge block is never a candidate
+        btab[i] = make_uint2(e.x, (e.x >> 24) ? kNoCandidate : block_depth(f, by, e));
+    };
+    int bx0 = 0, by0 = 0;
+    uint2 e0 = make_uint2(0u, 0u);
+    if (t < nbt) {
+        entry_pos(t, bx0, by0);
+        e0 = entry_load(bx0, by0);
+    }
 
-    // the non-zero words of the weight table likewise: lane t holds word t
-    // of every row
+    // the frame loads of all of a lane's quads of the tile and its halo.
+    // Quads outside the image read the nearest one inside: their luma is
+    // replaced below and their depths, those of a quad the window holds anyway
+    // where it is consulted, change no test.  Addresses are the tile's first
+    // row (uniform) and a 32-bit offset.
+    constexpr int NQ = T::NQ;
+    const int yb = max(ty0 - R, 0);
+    const size_t row0 = (size_t)yb * W;
+    const uint8_t* frame0 = f.frame + 3 * row0;
+    const int xl = (W - 1) & ~3;  // the row's last quad
+    uint3 vq[NQ];
+    uint32_t dq[NQ];
+    if (H > 0) {
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) {
+            const int i = t + NT * k;
+            if (NT * (k + 1) > TR * kTileQuads && i >= TR * kTileQuads) break;
+            const int tr = i / kTileQuads, tq = i - tr * kTileQuads;
+            const int yy = min(max(ty0 - R + tr, 0), H - 1), x0 = min(max(tx0 - 4 + 4 * tq, 0), xl);
+            const uint32_t o = __umul24(yy - yb, W) + x0;
+            vq[k] = load_quad_words<ALIGNED>(frame0 + 3u * o, W - x0);
+            if (f.depth_in) dq[k] = load_quad_bytes<false>(f.depth_in + row0 + o, W - x0);
+        }
+    }
+
+    // the non-zero words of the weight table: lane t holds word t of every row
     uint32_t wq[NK];
     {
         const uint32_t* src = kCbfWeights.w[(blockIdx.x + blockIdx.y) % kCbfCopies];
@@ -353,119 +406,93 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
         for (int k = 0; k < NK; ++k) wq[k] = nz ? src[k * kCbfWords + t - kCbfW0] : 0u;
     }
 
-    // the tile's block table (halo and one ring of neighbours, clipped to the
-    // grid) into LDS, so the raw depth needs no global lookups
-    // (clipped to the grid plus one ring outside it, whose entries are
-    // marked as edge blocks)
-    const int ks = __builtin_ctz((unsigned)f.K);
-    const int bx_lo = max(-1, ((tx0 - 4) >> ks) - 1), bx_hi = min(f.gw, ((tx0 + 4 * kTileQuads - 5) >> ks) + 1);
-    const int by_lo = max(-1, ((ty0 - R) >> ks) - 1), by_hi = min(f.gh, ((ty0 + kTileH - 1 + R) >> ks) + 1);
-    const int bw = bx_hi - bx_lo + 1;
-    if (!K2 && !f.depth_in && H > 0) {
-        const int nbt = bw * (by_hi - by_lo + 1);
-        // after the strip-parallel grouping (unless its merge grouped the
-        // whole frame itself) a block's region depth is resolved here from
-        // its component slot and the merge's slot table
-        const bool strips = f.rstrip > 0 && f.rctl[1] == 0;
-        for (int i = t; i < nbt; i += 256) {
-            const int r = i / bw;
-            const int by = by_lo + r, bx = bx_lo + (i - r * bw);
-            uint2 e = make_uint2(1u << 24, kNoCandidate);
-            if (by >= 0 && by < f.gh && bx >= 0 && bx < f.gw) {
-                e = f.binfo[by * f.gw + bx];
-                if (strips) e.y = block_depth_from_slots(f, by, e);
-                if (e.x >> 24) e.y = kNoCandidate;  // an edge block is never a candidate
-            }
-            btab[i] = e;
-        }
+    if (t < nbt) entry_store(t, by0, e0);
+    for (int i = t + NT; i < nbt; i += NT) {
+        int bx, by;
+        entry_pos(i, bx, by);
+        entry_store(i, by, entry_load(bx, by));
     }
 #pragma unroll
     for (int k = 0; k < NK; ++k) reinterpret_cast<uint32_t*>(wtab)[k * 256 + t] = wq[k];
+    if (t < kWtabTail) reinterpret_cast<uint32_t*>(wtab)[NK * 256 + t] = 0;
     if (t == 0) nwork = 0;
     __syncthreads();
+
+    auto store_df = [&](int x0_, int y_, uint32_t df4) {
+        const uint32_t o = __umul24(y_ - yb, W) + x0_;
+        store_quad_bytes<ALIGNED>(f.df + row0 + o, df4, W - x0_);
+        if (f.out_df) store_quad_bytes<false>(f.out_df + row0 + o, df4, W - x0_);
+    };
+
+    // a tile whose windows all lie in non-edge blocks of one region depth is
+    // that depth (blocks of 8 px and more: at most 10 x 6 blocks under the
+    // windows, one per lane in two steps)
+    bool uniform = false;
+    if (!K2 && !f.depth_in && wide && !f.out_d0) {
+        const int cx = min((max(tx0 - R, 0) >> ks) + (t & 15), min(tx0 + kTileW - 1 + R, W - 1) >> ks) - bx_lo;
+        const int b0 = max(ty0 - R, 0) >> ks, b1 = min(ty0 + TH - 1 + R, H - 1) >> ks;
+        const uint32_t c = btab[((ty0 >> ks) - by_lo) * bp + (tx0 >> ks) - bx_lo].y;
+        uint32_t bad = 0;
+        for (int b = b0 + ((t >> 4) & 3); b <= b1; b += 4) {
+            const uint2 e = btab[(b - by_lo) * bp + cx];
+            bad |= (e.x >> 24) | (e.y ^ c);
+        }
+        uniform = !__ballot(bad != 0);
+        if (uniform) {
+#pragma unroll
+            for (int half = 0; half < 16 * TH / NT; ++half) {
+                const int x0 = tx0 + 4 * (t & (kTileQ - 1)), y = ty0 + (t >> 4) + NT / 16 * half;
+                if (x0 < W && y < H) store_df(x0, y, c * 0x01010101u);
+            }
+        }
+    }
 
     // doubled luma + raw depth of the tile and its halo (columns tx0-4 ..
     // tx0+67)
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
-        const int i = t + 256 * k;
-        if (i >= TR * kTileQuads) break;
+        const int i = t + NT * k;
+        if ((NT * (k + 1) > TR * kTileQuads && i >= TR * kTileQuads) || uniform || H <= 0) break;
         const int tr = i / kTileQuads, tq = i - tr * kTileQuads;
-        const int yy = ty0 - R + tr;
-        const int x0 = tx0 - 4 + 4 * tq;
-        uint32_t y01 = 0, y23 = 0, d01 = 0, d23 = 0;
-        if (yy >= 0 && yy < H && x0 >= 0 && x0 < W) {
-            const int n = min(4, W - x0);
-            const uint8_t* p = f.frame + ((size_t)yy * W + x0) * 3;
-            uint32_t col[4], D[4];
-            if (ALIGNED) {
-                const uint3 v = in.vq[k];
-                quad_luma2(v, y01, y23);
-                quad_colours(v, col);
-            } else {
-                uint32_t Y[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (j < n) {
-                        Y[j] = 2u * (uint32_t)luma(p[3 * j], p[3 * j + 1], p[3 * j + 2]);
-                        col[j] = p[3 * j] | ((uint32_t)p[3 * j + 1] << 8) | ((uint32_t)p[3 * j + 2] << 16);
-                    } else {
-                        Y[j] = 0;
-                        col[j] = 0;
-                    }
-                }
-                y01 = Y[0] | (Y[1] << 16);
-                y23 = Y[2] | (Y[3] << 16);
-            }
-            if (f.depth_in) {
-                const uint8_t* dp = f.depth_in + (size_t)yy * W + x0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) D[j] = j < n ? dp[j] : 0u;
-            } else if (K2) {
-                quad_depth_k2(f, x0, yy, f.rstrip > 0 && f.rctl[1] == 0, col, D);
-            } else {
-                quad_depth_tab(f, x0, yy, ks, btab, bx_lo, by_lo, bw, col, D);
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) if (j >= n) D[j] = 0;
-            d01 = D[0] | (D[1] << 16);
-            d23 = D[2] | (D[3] << 16);
-            if (f.out_d0 && tr >= R && tr < R + kTileH && tq >= 1 && tq <= kTileQ) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (j < n) f.out_d0[(size_t)yy * W + x0 + j] = (uint8_t)D[j];
-            }
+        const int yo = ty0 - R + tr, xo = tx0 - 4 + 4 * tq;
+        const int yy = min(max(yo, 0), H - 1), x0 = min(max(xo, 0), xl);
+        const int n = W - x0;
+        uint32_t y01, y23, col[4], D[4];
+        quad_luma2(vq[k], y01, y23);
+        if (yy != yo || x0 != xo) y01 = y23 = kLumaOut * 0x10001u;
+        if (!ALIGNED && n < 4) {
+            if (n < 2) y01 = (y01 & 0xFFFFu) | (kLumaOut << 16);
+            y23 = n < 3 ? kLumaOut * 0x10001u : (y23 & 0xFFFFu) | (kLumaOut << 16);
         }
+        if (f.depth_in) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) D[j] = (dq[k] >> (8 * j)) & 255u;
+        } else {
+            quad_colours(vq[k], col);
+            if (K2) quad_depth_k2(f, x0, yy, col, D);
+            else quad_depth_tab(f, x0, yy, ks, btab, bx_lo, by_lo, bp, col, D);
+        }
+        if (!ALIGNED) {
+#pragma unroll
+            for (int j = 1; j < 4; ++j) if (j >= n) D[j] = 0;
+        }
+        if (f.out_d0 && yy == yo && x0 == xo && tr >= R && tr < R + TH && tq >= 1 && tq <= kTileQ)
+            store_quad_bytes<false>(f.out_d0 + (size_t)yy * W + x0, D[0] | (D[1] << 8) | (D[2] << 16) | (D[3] << 24), n);
         tY[tr * kRowWords + 2 * tq] = y01;
         tY[tr * kRowWords + 2 * tq + 1] = y23;
-        tD[tr * kRowWords + 2 * tq] = d01;
-        tD[tr * kRowWords + 2 * tq + 1] = d23;
+        tD[tr * kRowWords + 2 * tq] = D[0] | (D[1] << 16);
+        tD[tr * kRowWords + 2 * tq + 1] = D[2] | (D[3] << 16);
     }
     __syncthreads();
-
-    auto store_df = [&](int x0_, int y_, const uint32_t (&df)[4]) {
-        const int n = min(4, W - x0_);
-        const size_t o = (size_t)y_ * W + x0_;
-        if (ALIGNED) {
-            *reinterpret_cast<uint32_t*>(f.df + o) = df[0] | (df[1] << 8) | (df[2] << 16) | (df[3] << 24);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) if (j < n) f.df[o + j] = (uint8_t)df[j];
-        }
-        if (f.out_df) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) if (j < n) f.out_df[o + j] = (uint8_t)df[j];
-        }
-    };
 
     const int qx = t & (kTileQ - 1);
     const int lane = t & 63;
 #pragma unroll
-    for (int half = 0; half < 2; ++half) {
-        const int ty = (t >> 4) + 16 * half;
+    for (int half = 0; half < 16 * TH / NT; ++half) {
+        const int ty = (t >> 4) + NT / 16 * half;
         const int x0 = tx0 + 4 * qx, y = ty0 + ty;
         bool needs = false;
-        if (x0 < W && y < H) {
+        if (x0 < W && y < H && !uniform) {
             // exact shortcut: all in-window depths (columns x0-R .. x0+3+R,
             // rows inside the image) equal -> the normalised weighted sum is
             // that depth.  With blocks of 8 px or more the window's pixels
@@ -477,11 +504,11 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
             // is not uniform and goes to the filter without the pixel test:
             // the block-row steps of the background ramp are most of these)
             uint32_t c = 0, bad = 1, sure = 0;
-            if (!K2 && !f.depth_in && ks >= 3) {
+            if (!K2 && !f.depth_in && wide) {
                 const int bxa = max(x0 - R, 0) >> ks, bxb = min(x0 + 3 + R, W - 1) >> ks;
                 const int bya = max(y - R, 0) >> ks, byb = min(y + R, H - 1) >> ks;
-                const uint2 e00 = btab[(bya - by_lo) * bw + (bxa - bx_lo)], e01 = btab[(bya - by_lo) * bw + (bxb - bx_lo)];
-                const uint2 e10 = btab[(byb - by_lo) * bw + (bxa - bx_lo)], e11 = btab[(byb - by_lo) * bw + (bxb - bx_lo)];
+                const uint2 e00 = btab[16 * (bya - by_lo) + (bxa - bx_lo)], e01 = btab[16 * (bya - by_lo) + (bxb - bx_lo)];
+                const uint2 e10 = btab[16 * (byb - by_lo) + (bxa - bx_lo)], e11 = btab[16 * (byb - by_lo) + (bxb - bx_lo)];
                 c = e00.y;
                 const uint32_t edge = (e00.x | e01.x | e10.x | e11.x) >> 24;
                 const uint32_t differ = (e01.y ^ c) | (e10.y ^ c) | (e11.y ^ c);
@@ -505,8 +532,7 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
                 }
             }
             if (!bad) {
-                const uint32_t df[4] = {c, c, c, c};
-                store_df(x0, y, df);
+                store_df(x0, y, c * 0x01010101u);
             } else {
                 needs = true;
             }
@@ -517,7 +543,7 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
             int base = 0;
             if (lane == 0) base = atomicAdd(&nwork, __popcll(m));
             base = __shfl(base, 0);
-            if (needs) work[base + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(t + 256 * half);
+            if (needs) work[base + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(t + NT * half);
         }
     }
     __syncthreads();
@@ -526,34 +552,29 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
     // partner's two results by a lane shuffle and stores all four
     constexpr int PW = CbfPairWin<R>::kWords;
     const int nw2 = 2 * nwork;
-    for (int i0 = 0; i0 < nw2; i0 += 256) {
+    for (int i0 = 0; i0 < nw2; i0 += NT) {
         const int i = i0 + t;
         const bool on = i < nw2;
         const int q = on ? work[i >> 1] : 0;
         const int hf = i & 1;
-        const int qx_ = q & (kTileQ - 1), ty_ = (q & 255) / kTileQ + 16 * (q >> 8);
+        const int qx_ = q & (kTileQ - 1), ty_ = q / kTileQ;
         const int x0_ = tx0 + 4 * qx_, y_ = ty0 + ty_;
         uint32_t df2[2] = {0u, 0u};
         if (on) {
             // the pair's first pixel is LDS column 4 qx + 4 + 2 hf
             const int wb = 2 * qx_ + 2 + hf - CbfPairWin<R>::kW0;
-            uint32_t yw[S][PW], dw[S][PW], rows_ok = 0;
+            uint32_t yw[S][PW], dw[S][PW];
 #pragma unroll
             for (int r = 0; r < S; ++r) {
-                const int yy = y_ + r - R;
-                if (yy >= 0 && yy < H) rows_ok |= 1u << r;
                 const int base = (ty_ + r) * kRowWords + wb;
 #pragma unroll
                 for (int k = 0; k < PW; ++k) { yw[r][k] = tY[base + k]; dw[r][k] = tD[base + k]; }
             }
-            const int xp = x0_ + 2 * hf;
-            if (xp - R >= 0 && xp + 1 + R < W) cbf_pair<R, false>(yw, dw, rows_ok, xp, W, wtab, df2);
-            else cbf_pair<R, true>(yw, dw, rows_ok, xp, W, wtab, df2);
+            cbf_pair<R>(yw, dw, wtab, df2);
         }
         const uint32_t other = (uint32_t)__shfl_xor((int)(df2[0] | (df2[1] << 8)), 1);
         if (on && !hf) {
-            const uint32_t df[4] = {df2[0], df2[1], other & 255u, other >> 8};
-            store_df(x0_, y_, df);
+            store_df(x0_, y_, df2[0] | (df2[1] << 8) | (other << 16));
         }
     }
 }

@@ -119,6 +119,10 @@ __device__ __forceinline__ void store_quad_bytes(uint8_t* p, uint32_t v, int n) 
     }
 }
 
+// Second word of a block's table entry: its region depth with this flag, or
+// (without it) the slot its component has in the merge's table.
+constexpr uint32_t kResolved = 1u << 31;
+
 constexpr size_t kMaxLds = 160 * 1024;
 
 // The value of v, opaque to the optimiser: indices derived from it are

@@ -1,6 +1,7 @@
 """GPU tests of the kernels at the sizes where their variants meet: rows that
-do not start on a dword.  Every output is compared with the oracle byte for
-byte."""
+do not start on a dword, edges of the depth filter's tiles and the size at
+which its tile height changes.  Every output is compared with the oracle byte
+for byte."""
 import pytest
 
 import refs
@@ -44,3 +45,28 @@ def test_rows_off_the_dword_grid(ctx, w, h, off):
     refs.assert_views([b[off:off + n].cpu().view(h, w, 3) for b in bufs], want, f"{w}x{h} offset {off}")
     for b in bufs:
         assert bool((b[:off] == _GUARD).all()) and bool((b[off + n:] == _GUARD).all()), "bytes beside an output written"
+
+
+@pytest.mark.parametrize("w,h,K,r", [(64, 16, 8, 2), (65, 17, 8, 2), (63, 15, 4, 3), (68, 18, 4, 3), (128, 33, 8, 3),
+                                     (132, 31, 16, 1), (60, 48, 32, 2), (196, 50, 64, 3), (127, 64, 8, 0),
+                                     (4096, 768, 0, 2), (4096, 769, 0, 2), (4094, 769, 0, 3)])
+def test_filter_tile_edges(ctx, oracle_mod, w, h, K, r):
+    """Filter tiles cut by the frame's edges at every radius, and the largest
+    frame of 16-row tiles beside the smallest of 32-row ones: filtered depth
+    and views."""
+    from paper_2009_09501_amd import pstereo_params_init, pstereo_synthesize
+    dev = torch.device("cuda:0")
+    host = synth.gen_frame(700 + w + h + r, w, h, 12, 4.0)
+    f = torch.from_numpy(host).to(dev)
+    outs = [torch.empty_like(f) for _ in range(3)]
+    df = torch.empty((h, w), dtype=torch.uint8, device=dev)
+    B = min(20, w)
+    p = pstereo_params_init(max_disparity=B, block_size=K, cbf_radius=r, out_depth=df)
+    p.stream = torch.cuda.current_stream().cuda_stream
+    print(f"filter tiles: {w}x{h} K={K} r={r}", flush=True)
+    pstereo_synthesize(ctx.handle, f, w, h, p, *outs)
+    torch.cuda.synchronize()
+    refs.assert_views(outs, refs.views(("tiles", w, h, K, r), host, B, K=K, r=r), f"{w}x{h} K={K} r={r}")
+    if w * h < 1 << 17:
+        ref = oracle_mod.synthesize(host, B, K=K, r=r)
+        assert (df.cpu().numpy() == ref.Df).all()
