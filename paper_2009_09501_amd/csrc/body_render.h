@@ -122,7 +122,7 @@ __device__ __forceinline__ void quad_luma2(uint3 v, uint32_t& y01, uint32_t& y23
 // the row ramp, other blocks take their merged component's depth.
 __device__ __forceinline__ uint32_t block_depth(const FrameDesc& f, int by, uint2 e) {
     if (e.y & kResolved) return e.y & 255u;
-    const uint32_t v = (e.x >> 24) ? 256u : f.rfin[e.y];
+    const uint32_t v = (e.x >> 24) ? 256u : f.rlist[e.y];
     return ((v >> 8) & 1u) ? (uint32_t)ramp(by, f.gh) : (v & 255u);
 }
 

@@ -41,7 +41,7 @@ __global__ void __launch_bounds__(kRegionThreads) k_regions(FrameDesc f) {
 
 __global__ void __launch_bounds__(kStripLanes) k_rg_strip(FrameDesc f) {
     __shared__ uint32_t lds[rg_strip_lds_words()];
-    rg_strip_body(f, blockIdx.x, lds);
+    rg_strip_body(f, blockIdx.x, blockDim.x, lds);
 }
 
 __global__ void __launch_bounds__(kStripLanes) k_rg_merge(FrameDesc f) {
@@ -51,10 +51,6 @@ __global__ void __launch_bounds__(kStripLanes) k_rg_merge(FrameDesc f) {
 }
 
 __global__ void __launch_bounds__(256) k_rg_final(FrameDesc f) { rg_final_block(f, blockIdx.x * 256 + threadIdx.x); }
-
-__global__ void __launch_bounds__(64) k_clear_words(uint32_t* p, int n) {
-    for (int i = threadIdx.x; i < n; i += 64) p[i] = 0u;
-}
 
 // Whether two streams run beside each other.  k_probe_wait, launched on one
 // stream, waits -- bounded in wall-clock time (s_memrealtime counts at
@@ -121,14 +117,21 @@ LaunchSpec spec_regions(const FrameDesc& f) {
 }
 
 // Rows per strip: about one block per lane (two for rows wider than the
-// workgroup), 0 when a row does not fit a strip.
-int strip_rows(int gw) {
+// workgroup), 0 when a row does not fit a strip.  Narrow grids take strips of
+// six rows (unless that makes more than kMaxStrips): the unions inside a strip
+// walk its rows one after the other, which joining more strips does not
+// (640x360: 12-row strips 27.5 us a frame, six 26.5, two 26.8).
+int strip_rows(int gw, int gh) {
     if (gw < 1 || gw > kStripBlocks) return 0;
-    return gw <= kStripLanes ? kStripLanes / gw : 1;
+    if (gw > kStripLanes) return 1;
+    return std::min(kStripLanes / gw, std::max(6, (gh + kMaxStrips - 1) / kMaxStrips));
 }
 
+int strip_lanes(int gw, int rows) { return std::min(kStripLanes, (gw * rows + 63) / 64 * 64); }
+
 LaunchSpec spec_rg_strip(const FrameDesc& f) {
-    return {reinterpret_cast<const void*>(&k_rg_strip), dim3((f.gh + f.rstrip - 1) / f.rstrip), dim3(kStripLanes), 0};
+    return {reinterpret_cast<const void*>(&k_rg_strip), dim3((f.gh + f.rstrip - 1) / f.rstrip),
+            dim3(strip_lanes(f.gw, f.rstrip)), 0};
 }
 
 LaunchSpec spec_rg_merge(const FrameDesc& f) {
@@ -138,11 +141,6 @@ LaunchSpec spec_rg_merge(const FrameDesc& f) {
 
 LaunchSpec spec_rg_final(const FrameDesc& f) {
     return {reinterpret_cast<const void*>(&k_rg_final), dim3((f.gw * f.gh + 255) / 256), dim3(256), 0};
-}
-
-hipError_t launch_clear_words(uint32_t* p, int n, hipStream_t s) {
-    hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(64), 0, s, p, n);
-    return hipGetLastError();
 }
 
 hipError_t launch_probe(unsigned long long* w, unsigned long long token, hipStream_t wait_on, hipStream_t post_on) {

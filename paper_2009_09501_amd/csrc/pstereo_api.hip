@@ -33,21 +33,18 @@ struct BlockScratch {
     uint32_t* stats = nullptr;
     uint2* binfo = nullptr;
     int32_t* labels = nullptr;
-    uint2* rent = nullptr;
-    uint32_t* rrow = nullptr;
-    uint32_t* rfin = nullptr;
-    uint2* rbnd = nullptr;
-    uint32_t* rctl = nullptr;
+    uint32_t* rlist = nullptr;
+    uint32_t* rhdr = nullptr;
 };
 
 constexpr size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
 // Byte sizes of the tables of one set, in carving order: statistics, block
-// info, labels, slot entries, slot rows, slot finals, boundary candidates,
-// control words.
-constexpr size_t kBlkTableBytes[8] = {
-    PSTEREO_MAX_BLOCKS * 4, PSTEREO_MAX_BLOCKS * 8, PSTEREO_MAX_BLOCKS * 4, pstereo::kRegionSlots * 8,
-    pstereo::kRegionSlots * 4, pstereo::kRegionSlots * 4, pstereo::kBoundSlots * 8, 4 * 4};
+// info, labels, slot list, strip headers.
+constexpr int kBlkTables = 5;
+constexpr size_t kBlkTableBytes[kBlkTables] = {PSTEREO_MAX_BLOCKS * 4, PSTEREO_MAX_BLOCKS * 8, PSTEREO_MAX_BLOCKS * 4,
+                                               PSTEREO_MAX_BLOCKS * 4,
+                                               pstereo::kMaxStrips * pstereo::kStripHdrWords * 4};
 
 constexpr size_t block_scratch_bytes() {
     size_t tot = 0;
@@ -57,8 +54,8 @@ constexpr size_t block_scratch_bytes() {
 
 // Lay one set out in `mem` (block_scratch_bytes() bytes, 256-byte aligned).
 void block_scratch_carve(BlockScratch& b, uint8_t* mem) {
-    size_t off[8], tot = 0;
-    for (int i = 0; i < 8; ++i) {
+    size_t off[kBlkTables], tot = 0;
+    for (int i = 0; i < kBlkTables; ++i) {
         off[i] = tot;
         tot += align256(kBlkTableBytes[i]);
     }
@@ -66,21 +63,17 @@ void block_scratch_carve(BlockScratch& b, uint8_t* mem) {
     b.stats = reinterpret_cast<uint32_t*>(mem + off[0]);
     b.binfo = reinterpret_cast<uint2*>(mem + off[1]);
     b.labels = reinterpret_cast<int32_t*>(mem + off[2]);
-    b.rent = reinterpret_cast<uint2*>(mem + off[3]);
-    b.rrow = reinterpret_cast<uint32_t*>(mem + off[4]);
-    b.rfin = reinterpret_cast<uint32_t*>(mem + off[5]);
-    b.rbnd = reinterpret_cast<uint2*>(mem + off[6]);
-    b.rctl = reinterpret_cast<uint32_t*>(mem + off[7]);
+    b.rlist = reinterpret_cast<uint32_t*>(mem + off[3]);
+    b.rhdr = reinterpret_cast<uint32_t*>(mem + off[4]);
 }
 
-// Allocate and carve one set; the control words start at zero (the merge
-// kernel leaves them zero after each frame).
+// Allocate and carve one set.
 hipError_t block_scratch_alloc(BlockScratch& b) {
     uint8_t* mem = nullptr;
     hipError_t e = hipMalloc(&mem, block_scratch_bytes());
     if (e != hipSuccess) return e;
     block_scratch_carve(b, mem);
-    return hipMemset(b.rctl, 0, 4 * sizeof(uint32_t));
+    return hipSuccess;
 }
 
 // One filtered-depth image, rounded up so that the second one stays aligned.
@@ -417,12 +410,9 @@ int build_desc(pstereo_ctx* c, const uint8_t* frame, int w, int h, const pstereo
     f.binfo = bs.binfo;
     f.labels = bs.labels;
     f.df = c->d_df;
-    f.rent = bs.rent;
-    f.rrow = bs.rrow;
-    f.rfin = bs.rfin;
-    f.rbnd = bs.rbnd;
-    f.rctl = bs.rctl;
-    f.rstrip = pstereo::strip_rows(gw);
+    f.rlist = bs.rlist;
+    f.rhdr = bs.rhdr;
+    f.rstrip = pstereo::strip_rows(gw, gh);
     f.w = w;
     f.h = h;
     f.K = K;
@@ -589,11 +579,8 @@ int pstereo_synthesize(pstereo_ctx* c, const uint8_t* frame, int w, int h, const
         f.stats = bs.stats;
         f.binfo = bs.binfo;
         f.labels = bs.labels;
-        f.rent = bs.rent;
-        f.rrow = bs.rrow;
-        f.rfin = bs.rfin;
-        f.rbnd = bs.rbnd;
-        f.rctl = bs.rctl;
+        f.rlist = bs.rlist;
+        f.rhdr = bs.rhdr;
         if (deep) f.df = c->pipe_n % 2 ? c->d_df2 : c->d_df;
         ensure_overlap(c, s, deep);
         first = !c->pipe_valid || c->pipe_stream != s || c->pipe_deep != deep;
@@ -840,11 +827,8 @@ static FrameDesc video_desc(const pstereo_video* v, const FrameDesc& f, int k) {
     d.stats = bs.stats;
     d.binfo = bs.binfo;
     d.labels = bs.labels;
-    d.rent = bs.rent;
-    d.rrow = bs.rrow;
-    d.rfin = bs.rfin;
-    d.rbnd = bs.rbnd;
-    d.rctl = bs.rctl;
+    d.rlist = bs.rlist;
+    d.rhdr = bs.rhdr;
     return d;
 }
 
@@ -1098,9 +1082,6 @@ extern "C" int pstereo_synthesize_noalloc(int device, const uint8_t* frame, int 
         return rc;
     }
     hipError_t e = hipSetDevice(device);
-    // the grouping's control words start at zero on every call: an earlier
-    // call on this GPU may have stopped between its strips and its merge
-    if (e == hipSuccess && !f.depth_in) e = pstereo::launch_clear_words(f.rctl, 4, s);
     if (e != hipSuccess) return fail(nullptr, PSTEREO_E_DEVICE, "launch: %s", hipGetErrorString(e));
     pstereo::LaunchSpec ls[kMaxSpecs];
     int n;

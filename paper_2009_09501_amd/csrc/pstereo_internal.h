@@ -24,14 +24,10 @@ struct FrameDesc {
     int32_t* labels;         // per block: region label
     uint8_t* df;             // filtered depth scratch, u8 [h][w] (4-byte aligned)
     // strip-parallel region grouping (rstrip > 0): strip-local components are
-    // merged across strip boundaries through a table of slots; binfo then
-    // holds {statistics, slot of the block's component} until resolved
-    uint2* rent;             // per slot: {strip-local label, non-edge count}
-    uint32_t* rrow;          // per slot: lowest block row + 1
-    uint32_t* rfin;          // per slot: final label << 9 | background << 8 | depth
-    uint2* rbnd;             // boundary join candidates: {block above the strip, slot below}
-    uint32_t* rctl;          // [0]: slots taken, [1]: 1 if the merge fell back to one workgroup,
-                             // [2]: boundary candidates
+    // merged across strip boundaries through a list of slots; binfo then
+    // holds {statistics, slot of the block's component}
+    uint32_t* rlist;         // per slot: the strip's entry, then final label << 9 | background << 8 | depth
+    uint32_t* rhdr;          // per strip: slots, joins, then the join bits of its first row
     int rstrip;              // block rows per strip, 0 = single-workgroup grouping
     int w, h;
     int K, gw, gh;           // depth block size and grid
@@ -82,9 +78,12 @@ bool warp_shape_cap(int w, int cap, WarpShape* out);
 LaunchSpec spec_blockstats(const FrameDesc& f);
 LaunchSpec spec_regions(const FrameDesc& f);
 // Strip-parallel grouping: strips, merge, per-block resolution.
-int strip_rows(int gw);
-constexpr int kRegionSlots = 4096;
-constexpr int kBoundSlots = 8192;
+int strip_rows(int gw, int gh);
+int strip_lanes(int gw, int rows);
+constexpr int kRegionSlots = 4096;  // slots the merge holds in LDS
+constexpr int kMaxStrips = 64;      // a strip but the last holds more than 512 blocks
+constexpr int kStripHdrBits = 2;    // header word of the first join bits (2048 columns: 64 words)
+constexpr int kStripHdrWords = 66;
 LaunchSpec spec_rg_strip(const FrameDesc& f);
 LaunchSpec spec_rg_merge(const FrameDesc& f);
 LaunchSpec spec_rg_final(const FrameDesc& f);
@@ -116,8 +115,6 @@ inline hipError_t launch_timed(const LaunchSpec& ls, const FrameDesc& f, hipStre
     return hipExtLaunchKernel(ls.func, ls.grid, ls.block, args, ls.lds, s, start, stop, 0);
 }
 size_t regions_lds_bytes(int nb);
-// Zero n words with a kernel (no memset node, so it can sit in a captured graph).
-hipError_t launch_clear_words(uint32_t* p, int n, hipStream_t s);
 // Store v to *p (system-scope release) once everything before it on s is done.
 hipError_t launch_signal(unsigned long long* p, unsigned long long v, hipStream_t s);
 // Concurrency probe of two idle streams: a bounded wait on wait_on for a

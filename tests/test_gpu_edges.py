@@ -1,7 +1,9 @@
 """GPU tests of the kernels at the sizes where their variants meet: rows that
 do not start on a dword, edges of the depth filter's tiles and the size at
-which its tile height changes.  Every output is compared with the oracle byte
+which its tile height changes, and block grids at the limits of the region
+grouping's strips.  Every output is compared with the oracle byte
 for byte."""
+import numpy as np
 import pytest
 
 import refs
@@ -70,3 +72,46 @@ def test_filter_tile_edges(ctx, oracle_mod, w, h, K, r):
     if w * h < 1 << 17:
         ref = oracle_mod.synthesize(host, B, K=K, r=r)
         assert (df.cpu().numpy() == ref.Df).all()
+
+
+def _comb(gw, gh, K, every):
+    """Blocks of one colour with a block of another in every second column,
+    except in each ``every``-th block row: teeth that join row after row."""
+    img = np.full((gh * K, gw * K, 3), 90, np.uint8)
+    rows = np.arange(gh) % every != 0
+    odd = np.zeros((gh, gw), bool)
+    odd[np.ix_(rows, np.arange(gw) % 2 == 1)] = True
+    img[np.kron(odd, np.ones((K, K), bool))] = (104, 79, 107)  # nearly the same luma: no edge
+    return img
+
+
+@pytest.mark.parametrize("kind,gw,gh", [("still", 2048, 16), ("still", 1025, 31), ("still", 513, 63),
+                                        ("still", 170, 190), ("still", 171, 190), ("still", 80, 45),
+                                        ("still", 1, 2100), ("still", 64, 1), ("still", 2049, 15),
+                                        ("comb", 512, 64), ("comb", 341, 90), ("comb", 100, 60),
+                                        ("stripes", 1500, 20), ("stripes", 60, 66), ("stripes", 66, 68)])
+def test_grouping_strips(oracle_mod, kind, gw, gh):
+    """Grids of 2 px blocks at the strips' limits (rows wider than a
+    workgroup, one and many rows a strip, 63 strips), regions that join along
+    many columns, and more components than the merge holds: region labels,
+    depths and raw depth."""
+    from paper_2009_09501_amd import Context, pstereo_debug_blocks
+    K, w, h = 2, 2 * gw, 2 * gh
+    if kind == "still":
+        host = synth.gen_frame(gw + gh, w, h, 14, 3.0)
+    else:
+        host = _comb(gw, gh, K, 2 if kind == "comb" else gh + 1)
+    dev = torch.device("cuda:0")
+    ctx = Context(0, w, h)
+    try:
+        print(f"grouping {kind} {gw}x{gh} blocks", flush=True)
+        raw = torch.empty((h, w), dtype=torch.uint8, device=dev)
+        ctx.synthesize(torch.from_numpy(host).to(dev), max_disparity=2, block_size=K, cbf_radius=0, out_depth_raw=raw)
+        torch.cuda.synchronize()
+        ref = oracle_mod.synthesize(host, 2, K=K, r=0)
+        _, labels, dblk = pstereo_debug_blocks(ctx.handle)
+        assert np.array_equal(labels, ref.labels.reshape(gh, gw))
+        assert np.array_equal(dblk, ref.dblk.reshape(gh, gw))
+        assert np.array_equal(raw.cpu().numpy(), ref.D0)
+    finally:
+        ctx.close()
