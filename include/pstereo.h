@@ -70,7 +70,7 @@ extern "C" {
                                        A frame still filling pixels at sweep 4096 is not composed:
                                        the call returns PSTEREO_E_UNSUPPORTED and the outputs are
                                        left unwritten.  Plain calls only.  The first
-                                       such call allocates 12 * max_w * max_h bytes of scratch,
+                                       such call allocates 8 * max_w * max_h bytes of scratch,
                                        and every such call waits for its sweeps (the host checks
                                        convergence), so it is neither asynchronous nor
                                        graph-capturable */

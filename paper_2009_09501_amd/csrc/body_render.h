@@ -662,7 +662,7 @@ __device__ __forceinline__ void store_quad_views(const FrameDesc& f, int y, int 
         // the quad a row of another width ends with: byte stores of its pixels
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-            if (j >= n) break;
+            if (j >= n) continue;
             if (f.out_l) store_px_bytes(f.out_l + off + 3 * j, cl[j]);
             if (f.out_r) store_px_bytes(f.out_r + off + 3 * j, cr[j]);
             if (f.out_a) store_px_bytes(f.out_a + off + 3 * j, (cl[j] & 0xFFu) | (cr[j] & 0xFFFF00u));
@@ -851,6 +851,16 @@ __device__ __forceinline__ void fill_view(uint32_t qv, uint32_t oq, const uint32
     fill_quad<LEFT_TIES>(qv, oq, k, ex, hx, ef, hf, c, need);
 }
 
+// Block-iterative inpainting: tiles of kIpW x kIpH px, kIpSweeps sweeps a
+// launch.  A pixel's word is its colour below a tag: 0 as warped, kIpHole a
+// hole, else 1 + (sweep - 1) % (kIpSweeps * kIpCycle) of the sweep that filled
+// it (tags return to 0 every kIpCycle launches).
+constexpr int kIpW = 64, kIpH = 32;
+constexpr int kIpSweeps = kInpaintSweeps;
+constexpr int kIpCycle = 31;
+constexpr uint32_t kIpHole = 255u;
+static_assert(1 + kIpSweeps * kIpCycle < 254 && kMaxSweeps % kIpSweeps == 0, "tags fit beside the hole and the outside");
+
 // Image row y on NT lanes t = 0..NT-1 (whole waves) from the lane's loaded
 // share `in`; when next_y >= 0 the share of row next_y is loaded into `next`
 // while this row is resolved.  lds: warp_lds_bytes(w, NT, Q) bytes in the
@@ -983,21 +993,31 @@ __device__ __forceinline__ void warp_row_body(const FrameDesc& f, int y, int t, 
         }
     }
     if (f.ipc) {
-        // block-iterative inpainting follows: leave the warped colours and the
-        // holes, no row fill
+        // block-iterative inpainting follows: leave one word a pixel and the
+        // marks of the tiles that hold a hole, no row fill
         const size_t plane = (size_t)f.w * f.h;
+        const int ntx = (W + kIpW - 1) / kIpW, ntile = ntx * ((f.h + kIpH - 1) / kIpH);
 #pragma unroll
         for (int qi = 0; qi < Q; ++qi) {
             const int x0 = 4 * (qi * NT + t);
+            const uint32_t oq = (own >> (4 * qi)) & 15u;
+            if (!oq) continue;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int i = 4 * qi + j;
-                if (!((own >> i) & 1u)) continue;
-                const size_t o = (size_t)y * W + x0 + j;
-                f.ipc[o] = kl[i] & 0xFFFFFFu;
-                f.ipt[o] = ((vL >> i) & 1u) ? 0 : 0xFFFF;
-                f.ipc[plane + o] = kr[i] & 0xFFFFFFu;
-                f.ipt[plane + o] = ((vR >> i) & 1u) ? 0 : 0xFFFF;
+            for (int v = 0; v < 2; ++v) {
+                const uint32_t* k = v ? &kr[4 * qi] : &kl[4 * qi];
+                const uint32_t holes = oq & ~((v ? vR : vL) >> (4 * qi));
+                uint32_t w[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) w[j] = ((holes >> j) & 1u) ? kIpHole << 24 : k[j] & 0xFFFFFFu;
+                uint32_t* dst = f.ipc + plane * v + (size_t)y * W + x0;
+                if (oq == 15u) {
+                    __builtin_memcpy(dst, w, 16);
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 3; ++j)
+                        if ((oq >> j) & 1u) dst[j] = w[j];
+                }
+                if (holes) f.ipf[ntile * v + y / kIpH * ntx + x0 / kIpW] = 1u;
             }
         }
         clear_own();
@@ -1099,42 +1119,6 @@ __device__ __forceinline__ void gather_row(const FrameDesc& f, int y, int t, int
         }
         store_quad_views<ALIGNED>(f, y, x0, cl, cr);
     }
-}
-
-// One Jacobi sweep of the block-iterative inpainting over pixel p = (x, y) of
-// view v: a hole (tag 0xFFFF) with at least two undamaged 8-neighbours --
-// tag below `sweep`, so pixels filled in this same sweep do not count --
-// takes their per-channel mean rounded half up and the tag `sweep`.  Updates
-// in place are safe: a pixel written in this sweep is never read as
-// undamaged in it.  Returns 1 if p was filled.
-__device__ __forceinline__ int inpaint_pixel(const FrameDesc& f, int v, int x, int y, int sweep) {
-    const int W = f.w, H = f.h;
-    const size_t plane = (size_t)W * H * v;
-    const size_t o = plane + (size_t)y * W + x;
-    if (f.ipt[o] != 0xFFFF) return 0;
-    int cnt = 0;
-    uint32_t s0 = 0, s1 = 0, s2 = 0;
-#pragma unroll
-    for (int dy = -1; dy <= 1; ++dy) {
-#pragma unroll
-        for (int dx = -1; dx <= 1; ++dx) {
-            if (!dx && !dy) continue;
-            const int xx = x + dx, yy = y + dy;
-            if ((unsigned)xx >= (unsigned)W || (unsigned)yy >= (unsigned)H) continue;
-            const size_t q = plane + (size_t)yy * W + xx;
-            if ((int)f.ipt[q] >= sweep) continue;
-            const uint32_t c = f.ipc[q];
-            ++cnt;
-            s0 += c & 255u;
-            s1 += (c >> 8) & 255u;
-            s2 += c >> 16;
-        }
-    }
-    if (cnt < 2) return 0;
-    const uint32_t h = (uint32_t)cnt >> 1;
-    f.ipc[o] = ((s0 + h) / cnt) | (((s1 + h) / cnt) << 8) | (((s2 + h) / cnt) << 16);
-    f.ipt[o] = (uint16_t)sweep;
-    return 1;
 }
 
 // One image row (the single-row form used by the batch kernels), from and

@@ -118,9 +118,9 @@ struct pstereo_ctx {
     long long pipe_n = 0;
     // block-iterative inpainting scratch, allocated on first use
     uint32_t* d_ipc = nullptr;
-    uint16_t* d_ipt = nullptr;
+    uint32_t* d_ipf = nullptr;
     uint32_t* d_ipn = nullptr;
-    uint32_t* h_ipn = nullptr;  // pinned read-back of one sweep counter
+    uint32_t* h_done = nullptr;  // pinned: whether the last composition ran
     pstereo_batch* batch = nullptr;  // pstereo_synthesize_batch's batch object, made on first use
     char err[512] = {0};  // message of the last failure
     // last generated-depth call, for pstereo_debug_blocks
@@ -318,9 +318,9 @@ int pstereo_destroy(pstereo_ctx* c) {
     if (c->side) (void)hipStreamDestroy(c->side);
     if (c->mid) (void)hipStreamDestroy(c->mid);
     (void)hipFree(c->d_ipc);
-    (void)hipFree(c->d_ipt);
+    (void)hipFree(c->d_ipf);
     (void)hipFree(c->d_ipn);
-    if (c->h_ipn) (void)hipHostFree(c->h_ipn);
+    if (c->h_done) (void)hipHostFree(c->h_done);
     (void)hipGetLastError();
     delete c;
     return PSTEREO_OK;
@@ -490,21 +490,21 @@ int pstereo_synthesize(pstereo_ctx* c, const uint8_t* frame, int w, int h, const
         if (!c->d_ipc) {
             const size_t px = (size_t)c->max_w * c->max_h;
             if (hipMalloc(&c->d_ipc, 2 * px * sizeof(uint32_t)) != hipSuccess ||
-                hipMalloc(&c->d_ipt, 2 * px * sizeof(uint16_t)) != hipSuccess ||
-                hipMalloc(&c->d_ipn, (pstereo::kMaxSweeps + 1) * sizeof(uint32_t)) != hipSuccess ||
-                hipHostMalloc(&c->h_ipn, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
+                hipMalloc(&c->d_ipf, pstereo::inpaint_flags(c->max_w, c->max_h) * sizeof(uint32_t)) != hipSuccess ||
+                hipMalloc(&c->d_ipn, pstereo::kMaxSweeps / pstereo::kInpaintSweeps * sizeof(uint32_t)) != hipSuccess ||
+                hipHostMalloc(&c->h_done, sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) {
                 (void)hipGetLastError();
                 (void)hipFree(c->d_ipc);
-                (void)hipFree(c->d_ipt);
+                (void)hipFree(c->d_ipf);
                 (void)hipFree(c->d_ipn);
                 c->d_ipc = nullptr;
-                c->d_ipt = nullptr;
+                c->d_ipf = nullptr;
                 c->d_ipn = nullptr;
                 return fail(c, PSTEREO_E_NOMEM, "inpainting scratch allocation failed");
             }
         }
         f.ipc = c->d_ipc;
-        f.ipt = c->d_ipt;
+        f.ipf = c->d_ipf;
         f.ipn = c->d_ipn;
     }
 
@@ -608,6 +608,10 @@ int pstereo_synthesize(pstereo_ctx* c, const uint8_t* frame, int w, int h, const
         c->pipe_valid = false;
     }
 
+    if (inpaint && (e = pstereo::launch_inpaint_reset(f, s)) != hipSuccess) {
+        if (prof) ev_stage[0] = -1;  // nothing of this call is collected
+        return fail(c, PSTEREO_E_DEVICE, "inpainting launch: %s", hipGetErrorString(e));
+    }
     pstereo::LaunchSpec ls[kMaxSpecs];
     int stage[kMaxSpecs];
     int n;
@@ -645,28 +649,31 @@ int pstereo_synthesize(pstereo_ctx* c, const uint8_t* frame, int w, int h, const
     if (prof)
         for (int i = 0; i < kMaxKernels; ++i) ev_stage[i] = (int8_t)(i < n ? stage[i] : -1);
     if (inpaint) {
-        // sweeps in chunks of 8 until one fills nothing (each sweep returns at
-        // once after a sweep that filled nothing); a frame still filling
-        // pixels at the last allowed sweep is reported, not composed
-        if ((e = pstereo::launch_inpaint_reset(f, s)) != hipSuccess)
-            return fail(c, PSTEREO_E_DEVICE, "inpainting launch: %s", hipGetErrorString(e));
-        bool converged = false;
-        for (int sw = 1; sw <= pstereo::kMaxSweeps && !converged; sw += 8) {
-            const int last = std::min(sw + 7, pstereo::kMaxSweeps);
-            for (int k = sw; k <= last; ++k)
-                if ((e = pstereo::launch_inpaint_sweep(f, k, s)) != hipSuccess)
-                    return fail(c, PSTEREO_E_DEVICE, "inpainting sweep: %s", hipGetErrorString(e));
-            if ((e = hipMemcpyAsync(c->h_ipn, f.ipn + last, sizeof(uint32_t), hipMemcpyDeviceToHost, s)) != hipSuccess ||
-                (e = hipStreamSynchronize(s)) != hipSuccess)
+        // the sweeps in launches of eight (each returns at once after a
+        // launch whose last sweep filled nothing), some launches and a
+        // composition before the host looks: the composition runs only if
+        // the sweeps are done.  A hole between two pixels of a row is at most
+        // B wide and closes from both sides, one at the border at most B / 2
+        // and from one, so B / 2 sweeps and one that fills nothing come first;
+        // rows without a pixel take longer.  A frame still filling pixels at
+        // the last allowed sweep is reported, not composed
+        constexpr int kSweeps = pstereo::kInpaintSweeps, kLaunches = pstereo::kMaxSweeps / kSweeps;
+        bool composed = false;
+        for (int n = 0; n < kLaunches && !composed;) {
+            const int end = std::min(n == 0 ? (f.B / 2 + 2 + kSweeps - 1) / kSweeps : n + 16, kLaunches);
+            for (; n < end; ++n)
+                if ((e = pstereo::launch_inpaint_sweeps(f, n, s)) != hipSuccess)
+                    return fail(c, PSTEREO_E_DEVICE, "inpainting sweeps: %s", hipGetErrorString(e));
+            if ((e = pstereo::launch_inpaint_final(f, end - 1, c->h_done, s)) != hipSuccess)
+                return fail(c, PSTEREO_E_DEVICE, "inpainting composition: %s", hipGetErrorString(e));
+            if ((e = hipStreamSynchronize(s)) != hipSuccess)
                 return fail(c, PSTEREO_E_DEVICE, "inpainting convergence check: %s", hipGetErrorString(e));
-            converged = *c->h_ipn == 0;
+            composed = *(volatile uint32_t*)c->h_done == 1u;
         }
-        if (!converged)
+        if (!composed)
             return fail(c, PSTEREO_E_UNSUPPORTED,
                         "block inpainting still filled pixels at its last allowed sweep (%d); outputs not written",
                         pstereo::kMaxSweeps);
-        if ((e = pstereo::launch_inpaint_final(f, s)) != hipSuccess)
-            return fail(c, PSTEREO_E_DEVICE, "inpainting composition: %s", hipGetErrorString(e));
     }
     if (!ext) {
         c->have_blocks = true;

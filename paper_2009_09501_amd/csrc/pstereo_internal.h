@@ -34,12 +34,12 @@ struct FrameDesc {
     int B, T, g, tau, r;     // method parameters
     int aligned;             // w % 4 == 0 and every RGB24 pointer 4-byte aligned
     int gather;              // reconstruct by the Fig. 3 gather instead of the warp and fill
-    // block-iterative inpainting (ipc != null): the warp leaves, per view, the
-    // warped colour and a fill tag (0 landed, 0xFFFF hole, s = filled by sweep
-    // s) for the sweeps and the final composition
-    uint32_t* ipc;           // colours, [2][h][w]
-    uint16_t* ipt;           // tags, [2][h][w]
-    uint32_t* ipn;           // pixels filled per sweep, [kMaxSweeps + 1]
+    // block-iterative inpainting (ipc != null): the warp leaves, per view, a
+    // word of tag and colour per pixel and the marks of the tiles with holes
+    // for the sweeps and the final composition
+    uint32_t* ipc;           // tag << 24 | colour, [2][h][w]
+    uint32_t* ipf;           // tiles that hold a hole, [2][tiles]
+    uint32_t* ipn;           // pixels the last sweep of each launch filled
     // end-of-depth-map signal (pipelined calls): the grouping's last kernel
     // stores sig_value to *sig when it is done (null: no signal)
     unsigned long long* sig;
@@ -89,11 +89,15 @@ LaunchSpec spec_rg_merge(const FrameDesc& f);
 LaunchSpec spec_rg_final(const FrameDesc& f);
 LaunchSpec spec_cbf(const FrameDesc& f);
 LaunchSpec spec_warp(const FrameDesc& f, const WarpShape& ws);
-// Block-iterative inpainting: counter reset, one Jacobi sweep, composition.
+// Block-iterative inpainting: reset (before the warp), the sweeps in launches
+// of kInpaintSweeps, composition once launch `last` has filled nothing in its
+// last sweep (*done, in pinned host memory: 1 composed, 2 not done).
 constexpr int kMaxSweeps = 4096;
+constexpr int kInpaintSweeps = 8;
+size_t inpaint_flags(int w, int h);
 hipError_t launch_inpaint_reset(const FrameDesc& f, hipStream_t s);
-hipError_t launch_inpaint_sweep(const FrameDesc& f, int sweep, hipStream_t s);
-hipError_t launch_inpaint_final(const FrameDesc& f, hipStream_t s);
+hipError_t launch_inpaint_sweeps(const FrameDesc& f, int n, hipStream_t s);
+hipError_t launch_inpaint_final(const FrameDesc& f, int last, uint32_t* done, hipStream_t s);
 // Fig. 3 gather in place of the warp and the fill (one row per workgroup).
 bool gather_fits(int w);
 LaunchSpec spec_gather(const FrameDesc& f);

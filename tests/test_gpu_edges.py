@@ -1,7 +1,7 @@
 """GPU tests of the kernels at the sizes where their variants meet: rows that
 do not start on a dword, edges of the depth filter's tiles and the size at
-which its tile height changes, and block grids at the limits of the region
-grouping's strips.  Every output is compared with the oracle byte
+which its tile height changes, block grids at the limits of the region
+grouping's strips, and the sweeps of the block-iterative inpainting.  Every output is compared with the oracle byte
 for byte."""
 import numpy as np
 import pytest
@@ -115,3 +115,55 @@ def test_grouping_strips(oracle_mod, kind, gw, gh):
         assert np.array_equal(raw.cpu().numpy(), ref.D0)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("w,h,B", [(64, 32, 60), (65, 33, 60), (200, 97, 120), (129, 64, 255), (1, 40, 4), (640, 40, 255)])
+def test_inpaint_wide_holes(ctx, oracle_mod, w, h, B):
+    """Holes wider than a tile and its halo, tiles cut by the frame's edges:
+    an external depth map of far and near bands and boxes."""
+    from paper_2009_09501_amd.pstereo import PSTEREO_INPAINT_BLOCKS
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(w + h)
+    host = synth.gen_frame(w * 3 + h, w, h, 8, 4.0)
+    depth = np.zeros((h, w), np.uint8)
+    for _ in range(6):
+        x, y = rng.integers(0, w), rng.integers(0, h)
+        depth[y:y + 1 + h // 4, x:x + 1 + w // 5] = rng.integers(0, 256)
+    print(f"inpaint {w}x{h} B={B}", flush=True)
+    L, R, A = ctx.synthesize(torch.from_numpy(host).to(dev), depth=torch.from_numpy(depth).to(dev), max_disparity=B,
+                             cbf_radius=0, flags=PSTEREO_INPAINT_BLOCKS)
+    torch.cuda.synchronize()
+    ref = oracle_mod.synthesize(host, B, r=0, depth=depth)
+    for got, warp in ((L, ref.warpL), (R, ref.warpR)):
+        want, sweeps = oracle_mod.inpaint_blocks(host, warp)
+        assert np.array_equal(got.cpu().numpy(), want), f"{sweeps} sweeps"
+
+
+@pytest.mark.parametrize("h", [4096, 4097])
+def test_inpaint_last_allowed_sweep(ctx, oracle_mod, h):
+    """A frame whose rows below the first are all holes fills one row a sweep:
+    4095 hole rows are the most the sweeps allow; with one more the call is
+    refused and writes nothing."""
+    from paper_2009_09501_amd import PstereoError
+    from paper_2009_09501_amd.pstereo import PSTEREO_E_UNSUPPORTED, PSTEREO_INPAINT_BLOCKS
+    dev = torch.device("cuda:0")
+    w = 8
+    host = synth.gen_frame(h, w, h, 3, 4.0)
+    depth = np.full((h, w), 255, np.uint8)
+    depth[0] = 0
+    f, d = torch.from_numpy(host).to(dev), torch.from_numpy(depth).to(dev)
+    outs = tuple(torch.full_like(f, 7) for _ in range(3))
+    print(f"inpaint {h - 1} hole rows", flush=True)
+    kw = dict(out=outs, depth=d, max_disparity=255, depth_threshold=-1, cbf_radius=0, flags=PSTEREO_INPAINT_BLOCKS)
+    if h > 4096:
+        with pytest.raises(PstereoError) as ei:
+            ctx.synthesize(f, **kw)
+        assert ei.value.code == PSTEREO_E_UNSUPPORTED
+        torch.cuda.synchronize()
+        assert all(bool((o == 7).all()) for o in outs)
+        return
+    ctx.synthesize(f, **kw)
+    torch.cuda.synchronize()
+    ref = oracle_mod.synthesize(host, 255, T=-1, r=0, depth=depth)
+    want, _ = oracle_mod.inpaint_blocks(host, ref.warpL)
+    assert np.array_equal(outs[0].cpu().numpy(), want)
