@@ -327,9 +327,9 @@ def video_clip(torch, synth, bank: int):
 
 
 def video_leg(torch, synth, clip, steps: int, warmup: int, n_outs: int, stages: int):
-    """4K moving-ellipse video through the replayed kernel graphs (stages 2:
-    a frame's depth-map graph on the context's second stream during the
-    previous frame's filter and warp; 1: one stream): the frames of ``clip`` (frame numbers,
+    """4K moving-ellipse video through the video calls (stages 2: a frame's
+    depth map on the context's second stream during the previous frame's
+    filter and warp; 1: one stream): the frames of ``clip`` (frame numbers,
     device frames) in order, cycled when ``steps`` exceeds them, frame i into
     output triple i % ``n_outs``."""
     from paper_2009_09501_amd import Context, pstereo_params_init

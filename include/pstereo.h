@@ -246,26 +246,23 @@ int pstereo_synthesize_noalloc(int device, const uint8_t *frame, int w, int h, c
                                uint8_t *out_left, uint8_t *out_right, uint8_t *out_anaglyph);
 
 /*
- * Video: the frame's launch sequence captured once as a HIP graph and
- * replayed per frame (the paper converts video frame by frame, Section 5;
- * there is no state between frames).  pstereo_video_begin fixes the frame
- * size and parameters (generated depth only: no PSTEREO_DEPTH_EXTERNAL, no
- * depth dumps); the graph runs on p->stream (NULL = context stream).
- * pstereo_video_frame validates the buffers like pstereo_synthesize, writes
- * their pointers into the kernel arguments of one of eight instantiated
- * copies of the graph and launches it; it may wait for the replay made eight
- * to eleven frames earlier.  Frames on one video run in
- * order on its stream and share the context's scratch, so a context drives
- * one video (or plain calls on the same stream) at a time.
- * pstereo_video_end waits for the stream and frees the graphs.
- * With PSTEREO_PIPELINE in p->flags each copy is two graphs: the depth-map
- * stages, replayed on the context's second stream, and the filter and warp,
- * replayed on the video's stream after them; a frame's depth graph waits
- * only for what the video's stream held before the previous frame's call,
- * so it runs during that frame's filter and warp.  The caller then promises
- * that each frame was complete on the stream (or on the host) before the
- * previous pstereo_video_frame call was made -- frames are supplied one
- * ahead, as a decoder does.
+ * Video: frames of one size and one set of parameters, one call each (the
+ * paper converts video frame by frame, Section 5; there is no state between
+ * frames).  pstereo_video_begin fixes and checks the frame size and parameters
+ * (generated depth only: no PSTEREO_DEPTH_EXTERNAL, no depth dumps); the
+ * frames run on p->stream (NULL = the HIP null stream).
+ * pstereo_video_frame validates the buffers like pstereo_synthesize and
+ * launches the frame's kernels.  Frames on one video run in order on its
+ * stream and share the context's scratch, so a context drives one video (or
+ * plain calls on the same stream) at a time.
+ * pstereo_video_end waits for the stream and frees the video.
+ * With PSTEREO_PIPELINE in p->flags the depth-map stages go on the context's
+ * second stream and the filter and warp on the video's stream after them; a
+ * frame's depth map waits only for what the video's stream held before the
+ * previous frame's call, so it is built during that frame's filter and warp.
+ * The caller then promises that each frame was complete on the stream (or on
+ * the host) before the previous pstereo_video_frame call was made -- frames
+ * are supplied one ahead, as a decoder does.
  * Errors as for pstereo_synthesize; PSTEREO_E_UNSUPPORTED for the excluded
  * parameters.
  */

@@ -761,83 +761,29 @@ int pstereo_profile_collect(pstereo_ctx* c, double ms_sum[4], int* count, double
 
 
 // ------------------------------------------------------------------ video
-// The frame's launch sequence as HIP graphs, replayed per frame with the
-// frame and output pointers written into the kernel nodes' arguments.  A ring
-// of kRing instantiated copies lets the host prepare frame n+1 while frame n
-// runs; copy k is rewritten only after its previous replay (frame n - kRing)
-// has finished: completion events are recorded after every kEvery-th frame,
-// alternating between two events.  The region grouping reads only the
-// block tables and keeps its template arguments.
+// A fixed frame size and parameters, checked at begin; each frame's kernels
+// are launched directly.  (Replayed graphs of the same kernels were slower on
+// both sides: updating their arguments and launching two graphs cost the host
+// 51.5 us a frame, launching the kernels 26, and a replayed graph ran 5 us
+// longer on the GPU; 1920x1080 pipelined, 16 frames: 750-860 us -> 363.)
 //
-// Pipelined video (PSTEREO_PIPELINE at begin): each copy is two graphs, the
-// depth-map stages (replayed on the context's side stream) and the filter +
-// warp (on the video's stream, after the depth graph of the same frame), and
-// copy k works in block-table set k % 2; frame n's depth graph waits only for
-// what the video's stream held before frame n-1's call, so it runs during
-// frame n-1's filter and warp.
+// Pipelined video (PSTEREO_PIPELINE at begin): the depth-map stages go on the
+// context's side stream, the filter and warp on the video's stream after the
+// depth map of the same frame, and frame n works in block-table set n % 2; its
+// depth map waits only for what the video's stream held before frame n - 1's
+// call, so it is built during frame n - 1's filter and warp.
 struct pstereo_video {
-    static constexpr int kRing = 8;
-    static constexpr int kEvery = 4;
-    static_assert(kRing % 2 == 0, "ring copy k uses block-table set k % 2");
     pstereo_ctx* ctx = nullptr;
     int w = 0, h = 0;
     pstereo_params params{};
     hipStream_t stream = nullptr;
     bool pipe = false;
-    bool pipe_started = false;  // the previous frame went through the pipelined graphs
+    bool pipe_started = false;  // the previous frame's launches all went out
     // pipelined: frame numbers, [0] the last frame whose depth map is done,
     // [1] the last frame whose depth filter has started (both only grow)
     unsigned long long* d_sig = nullptr;
-    FrameDesc tmpl{};
-    WarpShape ws{};
-    pstereo::LaunchSpec ls[kMaxSpecs];
-    int stage[kMaxSpecs] = {};
-    bool per_frame[kMaxSpecs] = {};  // node i reads the frame / output pointers or a frame number
-    int gidx[kMaxSpecs] = {};        // node i's graph: 0, or 1 for the filter + warp of a pipelined video
-    int nk = 0;
-    hipGraph_t graph[2][kRing] = {};
-    hipGraphExec_t exec[2][kRing] = {};
-    hipGraphNode_t node[kRing][kMaxSpecs] = {};
-    hipEvent_t done[2] = {};
-    long long waited = -1;  // last event group known complete
     long long count = 0;
 };
-
-static void video_free(pstereo_video* v) {
-    for (int g = 0; g < 2; ++g) {
-        for (int k = 0; k < pstereo_video::kRing; ++k) {
-            if (v->exec[g][k]) (void)hipGraphExecDestroy(v->exec[g][k]);
-            if (v->graph[g][k]) (void)hipGraphDestroy(v->graph[g][k]);
-        }
-    }
-    for (int k = 0; k < 2; ++k)
-        if (v->done[k]) (void)hipEventDestroy(v->done[k]);
-    (void)hipFree(v->d_sig);
-    delete v;
-}
-
-static hipKernelNodeParams node_params(const pstereo::LaunchSpec& ls, void** args) {
-    hipKernelNodeParams kp{};
-    kp.blockDim = ls.block;
-    kp.gridDim = ls.grid;
-    kp.func = const_cast<void*>(ls.func);
-    kp.kernelParams = args;
-    kp.extra = nullptr;
-    kp.sharedMemBytes = (unsigned)ls.lds;
-    return kp;
-}
-
-// The descriptor of ring copy k: f with the block tables of its set.
-static FrameDesc video_desc(const pstereo_video* v, const FrameDesc& f, int k) {
-    FrameDesc d = f;
-    const BlockScratch& bs = v->ctx->blk[v->pipe ? k % 2 : 0];
-    d.stats = bs.stats;
-    d.binfo = bs.binfo;
-    d.labels = bs.labels;
-    d.rlist = bs.rlist;
-    d.rhdr = bs.rhdr;
-    return d;
-}
 
 int pstereo_video_begin(pstereo_ctx* c, int w, int h, const pstereo_params* p, pstereo_video** out) {
     if (!c) return PSTEREO_E_INVALID;
@@ -866,46 +812,24 @@ int pstereo_video_begin(pstereo_ctx* c, int w, int h, const pstereo_params* p, p
     v->params = pp;
     v->pipe = (pp.flags & PSTEREO_PIPELINE) != 0;
     uint32_t flags;
-    // template descriptor: aligned placeholders stand in for the frame buffers
-    // (the graphs run on p->stream, NULL = the HIP null stream)
+    // the size and parameters are checked here: aligned placeholders stand in
+    // for the frame buffers (the frames run on p->stream, NULL = the HIP null
+    // stream)
     uint8_t* ph = c->d_df;
-    int rc = build_desc(c, ph, w, h, &pp, ph + 4, ph + 8, ph + 12, &v->tmpl, &v->ws, &v->stream, &flags, false);
+    FrameDesc f;
+    WarpShape ws{};
+    int rc = build_desc(c, ph, w, h, &pp, ph + 4, ph + 8, ph + 12, &f, &ws, &v->stream, &flags, false);
     if (rc != PSTEREO_OK) {
         delete v;
         return rc;
     }
-    v->tmpl.out_l = v->tmpl.out_r = v->tmpl.out_a = nullptr;
-    v->tmpl.frame = nullptr;
-    v->tmpl.aligned = (w % 4 == 0);
-    frame_specs(v->tmpl, v->ws, v->ls, v->nk, &v->stage);
-    for (int i = 0; i < v->nk; ++i) {
-        // a pipelined video's last grouping kernel signals the frame's number
-        const bool signals = v->pipe && v->stage[i] == 1 && (i + 1 == v->nk || v->stage[i + 1] != 1);
-        v->per_frame[i] = v->stage[i] != 1 || signals;
-        v->gidx[i] = v->pipe && v->stage[i] >= 2 ? 1 : 0;
-    }
     hipError_t e = hipSetDevice(c->device);
     if (v->pipe && e == hipSuccess) ensure_overlap(c, v->stream, false);
     if (v->pipe && e == hipSuccess && (e = hipMalloc(&v->d_sig, 16)) == hipSuccess) e = hipMemset(v->d_sig, 0, 16);
-    for (int k = 0; k < pstereo_video::kRing && e == hipSuccess; ++k) {
-        FrameDesc arg = video_desc(v, v->tmpl, k);
-        void* args[] = {&arg};
-        for (int g = 0; g < (v->pipe ? 2 : 1) && e == hipSuccess; ++g) e = hipGraphCreate(&v->graph[g][k], 0);
-        int prev[2] = {-1, -1};  // last node added to each graph
-        for (int i = 0; i < v->nk && e == hipSuccess; ++i) {
-            const int g = v->gidx[i];
-            hipKernelNodeParams kp = node_params(v->ls[i], args);
-            hipGraphNode_t* dep = prev[g] >= 0 ? &v->node[k][prev[g]] : nullptr;
-            e = hipGraphAddKernelNode(&v->node[k][i], v->graph[g][k], dep, dep ? 1 : 0, &kp);
-            prev[g] = i;
-        }
-        for (int g = 0; g < (v->pipe ? 2 : 1) && e == hipSuccess; ++g)
-            e = hipGraphInstantiate(&v->exec[g][k], v->graph[g][k], nullptr, nullptr, 0);
-    }
-    for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&v->done[k], hipEventDisableTiming);
     if (e != hipSuccess) {
-        video_free(v);
-        return fail(c, PSTEREO_E_DEVICE, "graph setup: %s", hipGetErrorString(e));
+        (void)hipFree(v->d_sig);
+        delete v;
+        return fail(c, PSTEREO_E_DEVICE, "video setup: %s", hipGetErrorString(e));
     }
     *out = v;
     return PSTEREO_OK;
@@ -924,75 +848,55 @@ int pstereo_video_frame(pstereo_video* v, const uint8_t* frame, uint8_t* out_l, 
     hipError_t e = hipSetDevice(c->device);
     if (e != hipSuccess) return fail(c, PSTEREO_E_DEVICE, "hipSetDevice: %s", hipGetErrorString(e));
     c->pipe_valid = false;  // a later plain pipelined call waits for this frame
-    if (f.aligned != v->tmpl.aligned) {
-        // the captured kernels assume the first frame's alignment; launch
-        // directly on the stream, in set 0, after everything before
-        pstereo::LaunchSpec ls[kMaxSpecs];
-        int n;
-        frame_specs(f, ws, ls, n);
-        for (int i = 0; i < n; ++i)
-            if ((e = pstereo::launch(ls[i], f, s)) != hipSuccess)
-                return fail(c, PSTEREO_E_DEVICE, "launch: %s", hipGetErrorString(e));
-        v->pipe_started = false;  // the next frame's depth graph waits for this one
-        return PSTEREO_OK;
-    }
-    constexpr int R = pstereo_video::kRing, E = pstereo_video::kEvery;
-    const long long n = v->count;
-    const int k = (int)(n % R);
-    if (n >= R) {
-        // the previous replay of copy k (frame n - R) is covered by the event
-        // recorded after frame ((n - R) / E) * E + E - 1 < n
-        const long long g = (n - R) / E;
-        if (g > v->waited) {
-            if ((e = hipEventSynchronize(v->done[g % 2])) != hipSuccess)
-                return fail(c, PSTEREO_E_DEVICE, "event synchronize: %s", hipGetErrorString(e));
-            v->waited = g;
-        }
-    }
-    FrameDesc arg = video_desc(v, f, k);
-    const unsigned long long fn = (unsigned long long)n + 1;  // this frame's number
+    const unsigned long long fn = (unsigned long long)v->count + 1;  // this frame's number
     if (v->pipe) {
-        arg.sig = v->d_sig;
-        arg.sig_value = fn;
-        arg.mark = v->d_sig + 1;
-        arg.mark_value = fn;
-    }
-    void* args[] = {&arg};
-    for (int i = 0; i < v->nk; ++i) {
-        if (!v->per_frame[i]) continue;
-        hipKernelNodeParams kp = node_params(v->ls[i], args);
-        if ((e = hipGraphExecKernelNodeSetParams(v->exec[v->gidx[i]][k], v->node[k][i], &kp)) != hipSuccess)
-            return fail(c, PSTEREO_E_DEVICE, "graph node update: %s", hipGetErrorString(e));
-    }
-    if (v->pipe) {
-        // the depth graph once the previous frame's filter has started, so
+        const BlockScratch& bs = c->blk[v->count % 2];
+        f.stats = bs.stats;
+        f.binfo = bs.binfo;
+        f.labels = bs.labels;
+        f.rlist = bs.rlist;
+        f.rhdr = bs.rhdr;
+        f.sig = v->d_sig;
+        f.sig_value = fn;
+        f.mark = v->d_sig + 1;
+        f.mark_value = fn;
+        // the depth map once the previous frame's filter has started, so
         // after what the stream held before that frame's call (for the first
         // frame: after everything, an event); the filter and warp once the
-        // depth graph's grouping has signalled this frame's number (both
-        // through the video's words, polled by wait-value packets)
-        if ((!v->pipe_started && ((e = hipEventRecord(c->ev_before, v->stream)) != hipSuccess ||
-                                  (e = hipStreamWaitEvent(c->side, c->ev_before, 0)) != hipSuccess)) ||
-            (v->pipe_started &&
-             (e = hipStreamWaitValue64(c->side, v->d_sig + 1, fn - 1, hipStreamWaitValueGte, ~0ull)) != hipSuccess) ||
-            (e = hipGraphLaunch(v->exec[0][k], c->side)) != hipSuccess ||
-            (e = hipStreamWaitValue64(v->stream, v->d_sig, fn, hipStreamWaitValueGte, ~0ull)) != hipSuccess ||
-            (e = hipGraphLaunch(v->exec[1][k], v->stream)) != hipSuccess) {
-            v->pipe_started = false;
-            return fail(c, PSTEREO_E_DEVICE, "pipelined graph launch: %s", hipGetErrorString(e));
-        }
-        v->pipe_started = true;
-    } else if ((e = hipGraphLaunch(v->exec[0][k], v->stream)) != hipSuccess) {
-        return fail(c, PSTEREO_E_DEVICE, "graph launch: %s", hipGetErrorString(e));
+        // grouping has signalled this frame's number (both through the
+        // video's words, polled by wait-value packets)
+        e = v->pipe_started ? hipStreamWaitValue64(c->side, v->d_sig + 1, fn - 1, hipStreamWaitValueGte, ~0ull)
+                            : hipEventRecord(c->ev_before, s);
+        if (e == hipSuccess && !v->pipe_started) e = hipStreamWaitEvent(c->side, c->ev_before, 0);
     }
-    if (n % E == E - 1 && (e = hipEventRecord(v->done[(n / E) % 2], v->stream)) != hipSuccess)
-        return fail(c, PSTEREO_E_DEVICE, "event record: %s", hipGetErrorString(e));
+    pstereo::LaunchSpec ls[kMaxSpecs];
+    int stage[kMaxSpecs];
+    int nk;
+    frame_specs(f, ws, ls, nk, &stage);
+    for (int i = 0; i < nk && e == hipSuccess; ++i) {
+        if (v->pipe && stage[i] == 2) e = hipStreamWaitValue64(s, v->d_sig, fn, hipStreamWaitValueGte, ~0ull);
+        if (e == hipSuccess) e = pstereo::launch(ls[i], f, v->pipe && stage[i] <= 1 ? c->side : s);
+    }
+    if (e != hipSuccess) {
+        if (v->pipe) {
+            // drained, so that the next frame starts the pipeline again and no
+            // kernel of this one is still to store its number
+            (void)hipStreamSynchronize(c->side);
+            (void)hipStreamSynchronize(s);
+            (void)hipGetLastError();
+            v->pipe_started = false;
+            v->count++;
+        }
+        return fail(c, PSTEREO_E_DEVICE, "video frame: %s", hipGetErrorString(e));
+    }
+    v->pipe_started = v->pipe;
     v->count++;
     c->have_blocks = true;
-    c->last_fd = arg;
+    c->last_fd = f;
     c->blocks_final = f.rstrip == 0;
     c->last_gw = f.gw;
     c->last_gh = f.gh;
-    c->last_stream = v->stream;
+    c->last_stream = s;
     return PSTEREO_OK;
 }
 
@@ -1000,7 +904,8 @@ int pstereo_video_end(pstereo_video* v) {
     if (!v) return PSTEREO_OK;
     (void)hipSetDevice(v->ctx->device);
     (void)hipStreamSynchronize(v->stream);
-    video_free(v);
+    (void)hipFree(v->d_sig);
+    delete v;
     return PSTEREO_OK;
 }
 
