@@ -866,7 +866,7 @@ static_assert(1 + kIpSweeps * kIpCycle < 254 && kMaxSweeps % kIpSweeps == 0, "ta
 // while this row is resolved.  lds: warp_lds_bytes(w, NT, Q) bytes in the
 // state warp_prepare leaves, which the row restores.  Two barriers; inactive
 // lane groups do no memory work but pass them too.
-template <bool ALIGNED, int Q>
+template <bool ALIGNED, int Q, bool IP = false>
 __device__ __forceinline__ void warp_row_body(const FrameDesc& f, int y, int t, int NT, uint32_t* lds, bool active,
                                               const WarpRowIn<ALIGNED, Q>& in, int next_y,
                                               WarpRowIn<ALIGNED, Q>& next) {
@@ -992,7 +992,7 @@ __device__ __forceinline__ void warp_row_body(const FrameDesc& f, int y, int t, 
             }
         }
     }
-    if (f.ipc) {
+    if constexpr (IP) {
         // block-iterative inpainting follows: leave one word a pixel and the
         // marks of the tiles that hold a hole, no row fill
         const size_t plane = (size_t)f.w * f.h;
@@ -1123,7 +1123,7 @@ __device__ __forceinline__ void gather_row(const FrameDesc& f, int y, int t, int
 
 // One image row (the single-row form used by the batch kernels), from and
 // to any LDS contents.
-template <bool ALIGNED, int Q>
+template <bool ALIGNED, int Q, bool IP = false>
 __device__ __forceinline__ void warp_row(const FrameDesc& f, int y, int t, int NT, uint32_t* lds, bool active) {
     WarpRowIn<ALIGNED, Q> in, unused;
     if (active) {
@@ -1136,13 +1136,13 @@ __device__ __forceinline__ void warp_row(const FrameDesc& f, int y, int t, int N
     }
     warp_prepare(f, active ? f.w : 0, t, NT, lds);
     __syncthreads();
-    warp_row_body<ALIGNED, Q>(f, y, t, NT, lds, active, in, -1, unused);
+    warp_row_body<ALIGNED, Q, IP>(f, y, t, NT, lds, active, in, -1, unused);
 }
 
 // Rows y0, y0 + step, ... below y_end of the frame, the LDS state prepared
 // once, each row's loads issued during the previous row (one or two quads per
 // lane: a second row's share of four would not fit the registers).
-template <bool ALIGNED, int Q>
+template <bool ALIGNED, int Q, bool IP = false>
 __device__ __forceinline__ void warp_rows(const FrameDesc& f, int y0, int y_end, int step, int t, int NT,
                                           uint32_t* lds) {
     static_assert(Q < 4, "four quads per lane take one row at a time");
@@ -1153,7 +1153,7 @@ __device__ __forceinline__ void warp_rows(const FrameDesc& f, int y0, int y_end,
     __syncthreads();
     for (int y = y0; y < y_end; y += step) {
         const int ny = y + step < y_end ? y + step : -1;
-        warp_row_body<ALIGNED, Q>(f, y, t, NT, lds, true, cur, ny, nxt);
+        warp_row_body<ALIGNED, Q, IP>(f, y, t, NT, lds, true, cur, ny, nxt);
         cur = nxt;
     }
 }

@@ -34,22 +34,23 @@ __global__ void __launch_bounds__(256) k_cbf(FrameDesc f) {
 
 // Rows blockIdx.x, blockIdx.x + gridDim.x, ...: a grid of at most a few
 // workgroups per CU walks the rows, loading each next row during the current
-// one.
-template <bool ALIGNED, int Q>
+// one.  IP: block-iterative inpainting follows (a kernel of its own: the words
+// it leaves take a dozen registers more, two of seven waves per SIMD).
+template <bool ALIGNED, int Q, bool IP>
 __global__ void __launch_bounds__(512) k_warp(FrameDesc f) {
     extern __shared__ uint32_t lds[];
     warp_start_mark(f);
-    warp_rows<ALIGNED, Q>(f, blockIdx.x, f.h, gridDim.x, threadIdx.x, blockDim.x, lds);
+    warp_rows<ALIGNED, Q, IP>(f, blockIdx.x, f.h, gridDim.x, threadIdx.x, blockDim.x, lds);
 }
 
 // Rows needing four quads per lane (wider than 4096 px): one row per
 // workgroup of up to 1024 lanes (a second row's prefetched share would not
 // fit the register budget).
-template <bool ALIGNED>
+template <bool ALIGNED, bool IP>
 __global__ void __launch_bounds__(1024) k_warp_wide(FrameDesc f) {
     extern __shared__ uint32_t lds[];
     warp_start_mark(f);
-    warp_row<ALIGNED, 4>(f, blockIdx.x, threadIdx.x, blockDim.x, lds, true);
+    warp_row<ALIGNED, 4, IP>(f, blockIdx.x, threadIdx.x, blockDim.x, lds, true);
 }
 
 template <bool ALIGNED>
@@ -298,29 +299,41 @@ static LaunchSpec cbf_r(const FrameDesc& f) {
 
 LaunchSpec spec_cbf(const FrameDesc& f) { return f.aligned ? cbf_r<true>(f) : cbf_r<false>(f); }
 
-// VGPRs per lane of k_warp<aligned, quads 1 / 2>, read at preparation (every
-// context stores the same values).
-static std::atomic<int> g_warp_vgprs[2][2] = {{128, 128}, {128, 128}};
+// The row kernels by alignment, quads per lane (1, 2, 4) and inpainting.
+constexpr int kWarpFns = 12;
+static const void* warp_fn(bool aligned, int quads, bool ip) {
+    static const void* const fns[kWarpFns] = {
+        (const void*)&k_warp<false, 1, false>,   (const void*)&k_warp<false, 1, true>,
+        (const void*)&k_warp<false, 2, false>,   (const void*)&k_warp<false, 2, true>,
+        (const void*)&k_warp_wide<false, false>, (const void*)&k_warp_wide<false, true>,
+        (const void*)&k_warp<true, 1, false>,    (const void*)&k_warp<true, 1, true>,
+        (const void*)&k_warp<true, 2, false>,    (const void*)&k_warp<true, 2, true>,
+        (const void*)&k_warp_wide<true, false>,  (const void*)&k_warp_wide<true, true>};
+    return fns[(aligned ? 6 : 0) + (quads == 1 ? 0 : quads == 2 ? 2 : 4) + (ip ? 1 : 0)];
+}
+// Waves per SIMD their registers allow, read at preparation (every context
+// stores the same values).
+static std::atomic<int> g_warp_waves[kWarpFns];
 
-template <bool A>
-static LaunchSpec warp_q(const FrameDesc& f, const WarpShape& ws) {
-    if (ws.quads == 4)
-        return {reinterpret_cast<const void*>(&k_warp_wide<A>), dim3(f.h), dim3(ws.threads), ws.lds_bytes};
-    const void* fn = ws.quads == 1 ? reinterpret_cast<const void*>(&k_warp<A, 1>)
-                   : ws.quads == 2 ? reinterpret_cast<const void*>(&k_warp<A, 2>) : nullptr;
-    // resident workgroups per CU by LDS, lanes and registers (512 VGPRs per
-    // SIMD lane in steps of 8, at most 8 waves per SIMD, a workgroup's waves
-    // spread over the 4 SIMDs), times 256 CUs; every workgroup gets a row
-    const int regs = (g_warp_vgprs[A ? 1 : 0][ws.quads == 1 ? 0 : 1].load(std::memory_order_relaxed) + 7) / 8 * 8;
-    const int waves_simd = std::min(8, 512 / std::max(regs, 8));
+LaunchSpec spec_warp(const FrameDesc& f, const WarpShape& ws) {
+    const void* fn = warp_fn(f.aligned, ws.quads, f.ipc != nullptr);
+    if (ws.quads == 4) return {fn, dim3(f.h), dim3(ws.threads), ws.lds_bytes};
+    // resident workgroups per CU by LDS, lanes and registers (a workgroup's
+    // waves spread over the 4 SIMDs), times 256 CUs; every workgroup gets a
+    // row.  At 1920x1080 the scalar registers allow seven waves a SIMD where
+    // the vector ones alone would allow eight: three workgroups a CU, and a
+    // grid of four made the rest wait for a second round (768 workgroups 9.9
+    // us, 1024 11.1, 540 11.9)
+    int waves_simd = 8;
+    for (int i = 0; i < kWarpFns; ++i)
+        if (warp_fn(i >= 6, i % 6 < 2 ? 1 : i % 6 < 4 ? 2 : 4, i & 1) == fn)
+            waves_simd = g_warp_waves[i].load(std::memory_order_relaxed);
     const int by_regs = std::max(1, waves_simd / ((ws.threads / 64 + 3) / 4));
     const int by_lds = std::max(1, (int)(kMaxLds / std::max<size_t>(ws.lds_bytes, 1)));
     const int by_lanes = std::max(1, 2048 / ws.threads);
     const int resident = std::min(std::min(by_lds, by_lanes), by_regs) * 256;
     return {fn, dim3(std::min(f.h, resident)), dim3(ws.threads), ws.lds_bytes};
 }
-
-LaunchSpec spec_warp(const FrameDesc& f, const WarpShape& ws) { return f.aligned ? warp_q<true>(f, ws) : warp_q<false>(f, ws); }
 
 bool gather_fits(int w) { return gather_lds_bytes(w) <= kMaxLds; }
 
@@ -354,39 +367,18 @@ LaunchSpec spec_gather(const FrameDesc& f) {
     return {fn, dim3(f.h), dim3(256), gather_lds_bytes(f.w)};
 }
 
-template <bool A>
-static hipError_t allow_lds_wide() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_warp_wide<A>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
-}
-
-template <bool A, int Q>
-static hipError_t allow_lds() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_warp<A, Q>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
-}
-
-template <bool A, int Q>
-static hipError_t read_warp_vgprs() {
-    hipFuncAttributes a;
-    const hipError_t e = hipFuncGetAttributes(&a, reinterpret_cast<const void*>(&k_warp<A, Q>));
-    if (e == hipSuccess && a.numRegs > 0)
-        g_warp_vgprs[A ? 1 : 0][Q == 1 ? 0 : 1].store(a.numRegs, std::memory_order_relaxed);
-    return e;
-}
-
 hipError_t prepare_render_kernels() {
     hipError_t e;
-    if ((e = read_warp_vgprs<true, 1>()) != hipSuccess) return e;
-    if ((e = read_warp_vgprs<true, 2>()) != hipSuccess) return e;
-    if ((e = read_warp_vgprs<false, 1>()) != hipSuccess) return e;
-    if ((e = read_warp_vgprs<false, 2>()) != hipSuccess) return e;
-    if ((e = allow_lds<true, 1>()) != hipSuccess) return e;
-    if ((e = allow_lds<true, 2>()) != hipSuccess) return e;
-    if ((e = allow_lds<false, 1>()) != hipSuccess) return e;
-    if ((e = allow_lds<false, 2>()) != hipSuccess) return e;
-    if ((e = allow_lds_wide<true>()) != hipSuccess) return e;
-    if ((e = allow_lds_wide<false>()) != hipSuccess) return e;
+    for (int i = 0; i < kWarpFns; ++i) {
+        const void* fn = warp_fn(i >= 6, i % 6 < 2 ? 1 : i % 6 < 4 ? 2 : 4, i & 1);
+        if ((e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds)) != hipSuccess)
+            return e;
+        // one-wave workgroups without LDS: as many per CU as the registers
+        // (vector and scalar) let run
+        int waves = 0;
+        if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&waves, fn, 64, 0)) != hipSuccess) return e;
+        g_warp_waves[i].store(std::min(8, std::max(1, waves / 4)), std::memory_order_relaxed);
+    }
     if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gather<true>),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds)) != hipSuccess)
         return e;
