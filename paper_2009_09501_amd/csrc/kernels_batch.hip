@@ -252,10 +252,22 @@ __global__ void __launch_bounds__(256) k_mf_blockstats(const FrameDesc* frames, 
     }
 }
 
-__global__ void __launch_bounds__(kRegionThreads) k_mf_regions(const FrameDesc* frames) {
+// Region grouping: one workgroup per strip of every frame, then one per frame
+// for the merge (or for the whole grouping of a grid too wide for strips).
+// One workgroup a frame for all of it kept 64 CUs busy for 74 us of the
+// 64-frame batch; its 2,000 strips and 64 merges take 35.
+__global__ void __launch_bounds__(kStripLanes) k_mf_strip(const FrameDesc* frames, const int* first, int n) {
+    __shared__ uint32_t lds[rg_strip_lds_words()];
+    const int fi = frame_of(first, n, blockIdx.x);
+    const FrameDesc f = frames[fi];
+    rg_strip_body(f, blockIdx.x - first[fi], blockDim.x, lds);
+}
+
+__global__ void __launch_bounds__(kRegionThreads) k_mf_merge(const FrameDesc* frames) {
     extern __shared__ uint32_t lds[];
     const FrameDesc f = frames[blockIdx.x];
-    regions_body(f, lds);
+    if (f.rstrip > 0) rg_merge_body(f, lds);
+    else regions_body(f, lds);
 }
 
 // K2: every frame of the batch has blocks of 2 px (the block size is shared).
@@ -304,8 +316,10 @@ hipError_t launch_staged(const FrameDesc* d_frames, const int* d_first, const St
     const int n = pl.n;
     const int* first_bs = d_first;
     const int* first_cbf = d_first + (n + 1);
+    const int* first_strip = d_first + 2 * (n + 1);
     hipLaunchKernelGGL(k_mf_blockstats, dim3(pl.tiles_bs), dim3(256), 0, s, d_frames, first_bs, n, pl.bs_rows);
-    hipLaunchKernelGGL(k_mf_regions, dim3(n), dim3(kRegionThreads), pl.regions_lds, s, d_frames);
+    if (pl.strips) hipLaunchKernelGGL(k_mf_strip, dim3(pl.strips), dim3(pl.strip_lanes), 0, s, d_frames, first_strip, n);
+    hipLaunchKernelGGL(k_mf_merge, dim3(n), dim3(kRegionThreads), pl.merge_lds, s, d_frames);
     const void* cbf_fn;
     switch (pl.r) {
         case 0: cbf_fn = pl.k2 ? (const void*)&k_mf_cbf<0, true> : (const void*)&k_mf_cbf<0, false>; break;
@@ -319,7 +333,7 @@ hipError_t launch_staged(const FrameDesc* d_frames, const int* d_first, const St
         if (e != hipSuccess) return e;
     }
     for (int c = 0; c < pl.nclass; ++c) {
-        const int* fw = d_first + (size_t)(2 + c) * (n + 1);
+        const int* fw = d_first + (size_t)(3 + c) * (n + 1);
         const dim3 g(pl.cls_rows[c]), b(pl.cls_threads[c]);
         switch (pl.cls_q[c]) {
             case 1: hipLaunchKernelGGL(k_mf_warp<1>, g, b, pl.cls_lds[c], s, d_frames, fw, n, pl.warp_rows); break;
@@ -366,7 +380,7 @@ bool batch_width_ok(int w) {
 
 hipError_t prepare_batch_kernels() {
     hipError_t e;
-    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mf_regions), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds)) != hipSuccess) return e;
+    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mf_merge), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds)) != hipSuccess) return e;
     if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mf_warp<1>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds)) != hipSuccess) return e;
     if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mf_warp<2>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds)) != hipSuccess) return e;
     if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_mf_warp<4>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds)) != hipSuccess) return e;

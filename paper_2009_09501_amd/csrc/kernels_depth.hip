@@ -111,6 +111,7 @@ static LaunchSpec bs_k(const FrameDesc& f) {
 LaunchSpec spec_blockstats(const FrameDesc& f) { return f.aligned ? bs_k<true>(f) : bs_k<false>(f); }
 
 size_t regions_lds_bytes(int nb) { return regions_lds_bytes_c(nb); }
+size_t merge_lds_bytes(int nb) { return std::max(rg_merge_lds_words() * 4, regions_lds_bytes_c(nb)); }
 
 LaunchSpec spec_regions(const FrameDesc& f) {
     return {reinterpret_cast<const void*>(&k_regions), dim3(1), dim3(kRegionThreads), regions_lds_bytes(f.gw * f.gh)};
@@ -135,8 +136,7 @@ LaunchSpec spec_rg_strip(const FrameDesc& f) {
 }
 
 LaunchSpec spec_rg_merge(const FrameDesc& f) {
-    const size_t lds = std::max(rg_merge_lds_words() * 4, regions_lds_bytes(f.gw * f.gh));
-    return {reinterpret_cast<const void*>(&k_rg_merge), dim3(1), dim3(kStripLanes), lds};
+    return {reinterpret_cast<const void*>(&k_rg_merge), dim3(1), dim3(kStripLanes), merge_lds_bytes(f.gw * f.gh)};
 }
 
 LaunchSpec spec_rg_final(const FrameDesc& f) {

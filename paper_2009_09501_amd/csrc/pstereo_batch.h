@@ -41,7 +41,8 @@ constexpr int kMaxWarpClasses = 24;
 struct StagedPlan {
     int n = 0;
     int tiles_bs = 0, tiles_cbf = 0;
-    size_t regions_lds = 0;
+    int strips = 0, strip_lanes = 0;  // workgroups of the strip launch and their lanes
+    size_t merge_lds = 0;
     int r = 2;
     bool k2 = false;    // blocks of 2 px (shared by every frame of the batch)
     int warp_rows = 1;  // image rows per warp workgroup
@@ -53,8 +54,9 @@ struct StagedPlan {
     int cls_rows[kMaxWarpClasses];  // workgroups of each warp launch
 };
 
-// d_first: (2 + nclass) tables of n + 1 ints: first workgroup of each frame in
-// the block-statistics launch, the depth-filter launch, then each warp launch.
+// d_first: (3 + nclass) tables of n + 1 ints: first workgroup of each frame in
+// the block-statistics launch, the depth-filter launch, the strip launch, then
+// each warp launch.
 hipError_t launch_staged(const FrameDesc* d_frames, const int* d_first, const StagedPlan& plan, hipStream_t s);
 
 // Device scratch of one job: block tables (gw * gh entries each) and the

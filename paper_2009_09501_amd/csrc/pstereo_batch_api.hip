@@ -33,6 +33,7 @@ struct pstereo_batch {
     uint2* d_binfo = nullptr;
     int32_t* d_labels = nullptr;
     uint8_t* d_df = nullptr;
+    uint32_t* d_rhdr = nullptr;  // strip headers, kMaxStrips per job
     // pinned staging of the tables
     FrameDesc* h_frames = nullptr;
     BatchSeg* h_segs = nullptr;
@@ -98,6 +99,7 @@ void batch_free(pstereo_batch* b) {
     (void)hipFree(b->d_binfo);
     (void)hipFree(b->d_labels);
     (void)hipFree(b->d_df);
+    (void)hipFree(b->d_rhdr);
     (void)hipHostFree(b->h_frames);
     (void)hipHostFree(b->h_segs);
     (void)hipHostFree(b->h_need);
@@ -130,7 +132,8 @@ int batch_create_internal(pstereo_ctx* ctx, int max_jobs, int64_t max_pixels, bo
     }
     b->cus = prop.multiProcessorCount;
     b->grid = b->cus;  // fused form: one 1024-lane workgroup per CU
-    const size_t first_ints = (size_t)(2 + pstereo::kMaxWarpClasses) * (max_jobs + 1);
+    const size_t first_ints = (size_t)(3 + pstereo::kMaxWarpClasses) * (max_jobs + 1);
+    const size_t hdr_words = (size_t)pstereo::kMaxStrips * pstereo::kStripHdrWords;
     const size_t nb = PSTEREO_MAX_BLOCKS;
     const size_t df_bytes = (size_t)max_pixels + 256 * (size_t)max_jobs;
     bool ok = hipMalloc(&b->d_frames, sizeof(FrameDesc) * max_jobs) == hipSuccess &&
@@ -138,6 +141,7 @@ int batch_create_internal(pstereo_ctx* ctx, int max_jobs, int64_t max_pixels, bo
               hipMalloc(&b->d_need, sizeof(int) * 4 * max_jobs) == hipSuccess &&
               hipMalloc(&b->d_ctr, sizeof(uint32_t) * (pstereo::kXcds + 1 + 4 * max_jobs)) == hipSuccess &&
               hipMalloc(&b->d_first, sizeof(int) * first_ints) == hipSuccess &&
+              hipMalloc(&b->d_rhdr, sizeof(uint32_t) * hdr_words * max_jobs) == hipSuccess &&
               hipHostMalloc(&b->h_first, sizeof(int) * first_ints, hipHostMallocDefault) == hipSuccess &&
               (!own_scratch || (hipMalloc(&b->d_stats, sizeof(uint32_t) * nb * max_jobs) == hipSuccess &&
                                 hipMalloc(&b->d_binfo, sizeof(uint2) * nb * max_jobs) == hipSuccess &&
@@ -252,6 +256,11 @@ int batch_prepare_internal(pstereo_batch* b, const pstereo_job* jobs, int n, con
             f.df = b->d_df + df_off;
             df_off += ((size_t)j.w * j.h + 255) / 256 * 256;
         }
+        // the staged form's grouping: no batch dumps its labels, so their
+        // array holds the slot list
+        f.rlist = reinterpret_cast<uint32_t*>(f.labels);
+        f.rhdr = b->d_rhdr + (size_t)i * pstereo::kMaxStrips * pstereo::kStripHdrWords;
+        f.rstrip = pstereo::strip_rows(gw, gh);
         f.w = j.w;
         f.h = j.h;
         f.K = K;
@@ -347,6 +356,7 @@ int batch_prepare_internal(pstereo_batch* b, const pstereo_job* jobs, int n, con
         pl.bs_rows = b->tune.bs_rows;
         int* fb = b->h_first;
         int* fc = b->h_first + (n + 1);
+        int* fs = b->h_first + 2 * (n + 1);
         int nb_max = 1;
         std::vector<int> cls(n);
         for (int i = 0; i < n; ++i) {
@@ -358,6 +368,11 @@ int batch_prepare_internal(pstereo_batch* b, const pstereo_job* jobs, int n, con
             fc[i] = pl.tiles_cbf;
             (void)pstereo::batch_tasks(f, 2, &items, &gx);  // depth-filter tiles
             pl.tiles_cbf += items;
+            fs[i] = pl.strips;
+            if (f.rstrip > 0) {
+                pl.strips += (f.gh + f.rstrip - 1) / f.rstrip;
+                pl.strip_lanes = std::max(pl.strip_lanes, pstereo::strip_lanes(f.gw, f.rstrip));
+            }
             nb_max = std::max(nb_max, f.gw * f.gh);
             pstereo::WarpShape ws;
             if (!pstereo::warp_shape_cap(f.w, b->tune.warp_lanes, &ws))
@@ -376,9 +391,10 @@ int batch_prepare_internal(pstereo_batch* b, const pstereo_job* jobs, int n, con
         }
         fb[n] = pl.tiles_bs;
         fc[n] = pl.tiles_cbf;
-        pl.regions_lds = pstereo::regions_lds_bytes(nb_max);
+        fs[n] = pl.strips;
+        pl.merge_lds = pstereo::merge_lds_bytes(nb_max);
         for (int c = 0; c < pl.nclass; ++c) {
-            int* fw = b->h_first + (size_t)(2 + c) * (n + 1);
+            int* fw = b->h_first + (size_t)(3 + c) * (n + 1);
             int acc = 0;
             for (int i = 0; i < n; ++i) {
                 fw[i] = acc;
@@ -389,7 +405,7 @@ int batch_prepare_internal(pstereo_batch* b, const pstereo_job* jobs, int n, con
         }
         b->ntask = pl.tiles_bs + n + pl.tiles_cbf;
         if ((e = hipMemcpyAsync(b->d_frames, b->h_frames, sizeof(FrameDesc) * n, hipMemcpyHostToDevice, st)) != hipSuccess ||
-            (e = hipMemcpyAsync(b->d_first, b->h_first, sizeof(int) * (2 + pl.nclass) * (n + 1), hipMemcpyHostToDevice,
+            (e = hipMemcpyAsync(b->d_first, b->h_first, sizeof(int) * (3 + pl.nclass) * (n + 1), hipMemcpyHostToDevice,
                                 st)) != hipSuccess ||
             (e = hipEventRecord(b->staged, st)) != hipSuccess)
             return bfail(b, PSTEREO_E_DEVICE, "table upload: %s", hipGetErrorString(e));

@@ -257,9 +257,8 @@ int launch_lane(pstereo_server* s, Lane& ln) {
     p.stream = ln.st;
     int rc = PSTEREO_OK;
     if (s->policy == PSTEREO_SERVE_BATCH && n == 1 && lane_context(s, ln, jobs[0].w, jobs[0].h)) {
-        // a batch of one frame: the per-frame launch sequence, whose
-        // strip-parallel grouping beats the batch's one-workgroup grouping of
-        // a whole frame
+        // a batch of one frame: the per-frame launch sequence, which uploads
+        // no tables and picks its launch shapes for that frame
         p.max_disparity = jobs[0].max_disparity;
         rc = pstereo_synthesize(ln.ctx, jobs[0].frame, jobs[0].w, jobs[0].h, &p, jobs[0].out_left, jobs[0].out_right,
                                 jobs[0].out_anaglyph);
