@@ -606,9 +606,11 @@ int pstereo_synthesize_batch(pstereo_ctx* ctx, const pstereo_job* jobs, int n, c
             pstereo::ctx_set_error(ctx, "batch scratch allocation failed");
             return rc;
         }
-        // the staged form with 512-lane row workgroups of 4 rows, the tuning
-        // the autotuner picks for the uneven 720p..8K mix
-        b->tune = {PSTEREO_BATCH_STAGED, 512, 4, 0, 0};
+        // the staged form with 512-lane row workgroups of 4 rows and 64-row
+        // block-statistics tiles, the tuning the autotuner picks for the
+        // uneven 720p..8K mix (64 frames: 1640 us; 2 rows 1692, 256 lanes
+        // 1699, 1024 lanes 1788, tiles of 16 or 32 rows 1703 and 1678)
+        b->tune = {PSTEREO_BATCH_STAGED, 512, 4, 0, 64};
         *slot = b;
     }
     const int rc = pstereo_batch_run(b, jobs, n, p);

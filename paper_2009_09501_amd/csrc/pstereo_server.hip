@@ -409,6 +409,14 @@ int pstereo_server_create(int device, int64_t hbm_budget_bytes, int max_streams,
             server_free(s);
             return rc;
         }
+        // a lane's batches are small: few rows a workgroup, and 32-row
+        // block-statistics tiles whatever the block size (burst of 16 frames:
+        // 932 us; the batch object's defaults, 256 lanes, one row and 64-row
+        // tiles, 968)
+        if (ln.batch) {
+            const pstereo_batch_tuning tune = {PSTEREO_BATCH_STAGED, 512, 2, 0, 32};
+            (void)pstereo_batch_set_tuning(ln.batch, &tune);
+        }
     }
     s->worker = std::thread(scheduler, s);
     *out = s;
