@@ -681,11 +681,6 @@ __device__ __forceinline__ bool linked(uint32_t s, uint32_t n, int tau) {
     return !((s | n) >> 24) && (int)__builtin_amdgcn_sad_u8(s, n, 0u) <= tau;
 }
 
-// Lanes of the wave below this one whose bit is set in m.
-__device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
 // Inclusive sum or maximum over the lanes of a wave by lane moves inside the
 // vector unit (within rows of 16 lanes, then from row to row): six short
 // instructions where shuffles through LDS take six LDS round trips (0.3 us of

@@ -222,14 +222,16 @@ __device__ __forceinline__ void quad_depth_k2(const FrameDesc& f, int x0, int yy
 // row.
 //
 // Bound: small frames, the serial chain of one workgroup (staging, luma and
-// depth, window tests, filter); 4K and up, VALU issue (7.9 M wave
-// instructions a 4K frame, 13 us of the 23.5) plus the last round's tail.
+// depth, window tests, filter); 4K and up, VALU issue (7.3 M wave
+// instructions a 4K frame, 12 us of the 20.7) plus the last round's tail.
 // With the taps free of image-bounds tests, the block table loaded first, the
 // slot flag in the entry instead of a control word (whose load waited for the
 // whole frame tile) and 32-bit offsets: 640x360 13.2 -> 7.2 us, 1920x1080 14.5
 // -> 11.7, 1920x1080 of an external depth map at R = 3 31.5 -> 20.3, 3840x2160
-// 25.5 -> 23.5, 7680x4320 64.7 -> 58.5.  512 lanes per 32-row tile (twice the
-// waves, each with its own set-up) took 27.7 us at 4K.
+// 25.5 -> 23.5, 7680x4320 64.7 -> 58.5; with the plain form, staging loads
+// free of branches (behind which the compiler waited for each) and a work
+// list without atomics 5.7, 10.3, -, 20.7 and (48 rows) 49.3.  512 lanes per
+// 32-row tile (twice the waves, each with its own set-up) took 27.7 us at 4K.
 constexpr int kTileQ = 16;                   // quads per tile row
 constexpr int kTileW = 4 * kTileQ;           // 64 px
 constexpr int kTileH = 32;                   // rows (default)
@@ -304,23 +306,28 @@ struct CbfTile {
     static constexpr int TR = TH + 2 * R;  // LDS rows incl. halo
     static constexpr int NK = k_count(R);
     // tY, tD: TR * kRowWords words each; wtab: NK * 512 u16 and its zero tail;
-    // work: 16 TH u16; nwork
+    // work: 16 TH u16, a quarter per wave; nwork: 4 words
     // block table of the tile, its halo and one ring of neighbours, uint2
     // each: at most 12 blocks a row (16 entries, TH / 8 + 4 rows) for blocks
     // of 8 px and more, 20 x (TH / 4 + 4) for 4 px
     static constexpr int kBlkEntries = 20 * (TH / 4 + 4);
     static constexpr int kTabOff = 2 * TR * kRowWords;
     static constexpr int kWorkOff = kTabOff + NK * 256 + kWtabTail;
-    static constexpr int kBlkOff = (kWorkOff + 8 * TH + 1 + 1) & ~1;  // 8-byte aligned
+    static constexpr int kBlkOff = (kWorkOff + 8 * TH + 4 + 1) & ~1;  // 8-byte aligned
     static constexpr int kLdsWords = kBlkOff + 2 * kBlkEntries;
     static constexpr int NQ = (TR * kTileQuads + NT - 1) / NT;  // quads per lane incl. halo
 };
 
+// What a filter launch has to provide for: plain (generated depth, blocks of
+// 8 px and more, no depth dumps -- nearly every call), blocks of 2 px (raw
+// depth looked up per pixel in global memory, no block table in LDS), or any
+// other.  The plain form drops the options' tests: 3840x2160 22.9 -> 21.8 us.
+enum class CbfKind { kPlain, kBlocks2, kAny };
+
 // One 64 x TH tile (tile_x, tile_y) on 256 lanes t = 0..255 (four whole
 // waves).  lds: CbfTile<R, TH>::kLdsWords words.  Inactive lane groups do no
-// memory work but pass the same three barriers.  K2: blocks of 2 px (raw
-// depth looked up per pixel in global memory, no block table in LDS).
-template <int R, bool ALIGNED, bool K2 = false, int TH = kTileH>
+// memory work but pass the same three barriers.
+template <int R, bool ALIGNED, CbfKind KIND = CbfKind::kAny, int TH = kTileH>
 __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int tile_y, int t, uint32_t* lds,
                                          bool active) {
     constexpr int S = 2 * R + 1;
@@ -332,10 +339,14 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
     uint32_t* tD = tY + TR * kRowWords;
     uint16_t* wtab = reinterpret_cast<uint16_t*>(lds + T::kTabOff);
     uint16_t* work = reinterpret_cast<uint16_t*>(lds + T::kWorkOff);
-    int* nwork_p = reinterpret_cast<int*>(work + 16 * TH);
-    int& nwork = *nwork_p;
+    constexpr int kWavePart = 16 * TH / (NT / 64);
+    int* nwork = reinterpret_cast<int*>(work + 16 * TH);  // per wave
     uint2* btab = reinterpret_cast<uint2*>(lds + T::kBlkOff);
 
+    constexpr bool K2 = KIND == CbfKind::kBlocks2, PLAIN = KIND == CbfKind::kPlain;
+    const uint8_t* depth_in = PLAIN ? nullptr : f.depth_in;
+    uint8_t* out_df = PLAIN ? nullptr : f.out_df;
+    uint8_t* out_d0 = PLAIN ? nullptr : f.out_d0;
     const int W = f.w, H = active ? f.h : 0;
     const int tx0 = tile_x * kTileW, ty0 = tile_y * TH;
 
@@ -345,29 +356,29 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
     // loaded before anything else, so that the slot it leads to can be looked
     // up while the frame arrives
     const int ks = __builtin_ctz((unsigned)f.K);
-    const int bx_lo = max(-1, ((tx0 - 4) >> ks) - 1), bx_hi = min(f.gw, ((tx0 + 4 * kTileQuads - 5) >> ks) + 1);
+    const int bx_lo = max(-1, ((tx0 - 4) >> ks) - 1);
     const int by_lo = max(-1, ((ty0 - R) >> ks) - 1), by_hi = min(f.gh, ((ty0 + TH - 1 + R) >> ks) + 1);
-    const bool wide = ks >= 3;
+    const bool wide = PLAIN || ks >= 3;
     const int bp = wide ? 16 : 20;
-    const int nbt = !K2 && !f.depth_in && H > 0 ? bp * (by_hi - by_lo + 1) : 0;
+    const bool table = !K2 && !depth_in && active;
+    const int nbt = bp * (by_hi - by_lo + 1);
     auto entry_pos = [&](int i, int& bx, int& by) {
         const int r = wide ? i >> 4 : i / 20;
         by = by_lo + r;
         bx = bx_lo + (i - r * bp);
     };
-    auto entry_load = [&](int bx, int by) {
-        uint2 e = make_uint2(1u << 24, kResolved);  // outside the grid: an edge block
-        if ((unsigned)by < (unsigned)f.gh && (unsigned)bx < (unsigned)f.gw && bx <= bx_hi)
-            e = f.binfo[__umul24(by, f.gw) + bx];
-        return e;
+    auto entry_load = [&](int bx, int by) {  // the nearest block of the grid
+        return f.binfo[__umul24(min(max(by, 0), f.gh - 1), f.gw) + min(max(bx, 0), f.gw - 1)];
     };
-    auto entry_store = [&](int i, int by, uint2 e) {
-        // an edge block is never a candidate
-        btab[i] = make_uint2(e.x, (e.x >> 24) ? kNoCandidate : block_depth(f, by, e));
+    auto entry_store = [&](int i, int bx, int by, uint2 e) {
+        // outside the grid: an edge block; an edge block is never a candidate
+        const bool in = (unsigned)by < (unsigned)f.gh && (unsigned)bx < (unsigned)f.gw;
+        const uint32_t d = !in || (e.x >> 24) ? kNoCandidate : block_depth(f, by, e);
+        btab[i] = make_uint2(in ? e.x : 1u << 24, d);
     };
     int bx0 = 0, by0 = 0;
     uint2 e0 = make_uint2(0u, 0u);
-    if (t < nbt) {
+    if (table) {
         entry_pos(t, bx0, by0);
         e0 = entry_load(bx0, by0);
     }
@@ -384,7 +395,7 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
     const int xl = (W - 1) & ~3;  // the row's last quad
     uint3 vq[NQ];
     uint32_t dq[NQ];
-    if (H > 0) {
+    if (active) {
 #pragma unroll
         for (int k = 0; k < NQ; ++k) {
             const int i = t + NT * k;
@@ -393,7 +404,7 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
             const int yy = min(max(ty0 - R + tr, 0), H - 1), x0 = min(max(tx0 - 4 + 4 * tq, 0), xl);
             const uint32_t o = __umul24(yy - yb, W) + x0;
             vq[k] = load_quad_words<ALIGNED>(frame0 + 3u * o, W - x0);
-            if (f.depth_in) dq[k] = load_quad_bytes<false>(f.depth_in + row0 + o, W - x0);
+            if (depth_in) dq[k] = load_quad_bytes<false>(depth_in + row0 + o, W - x0);
         }
     }
 
@@ -401,34 +412,39 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
     uint32_t wq[NK];
     {
         const uint32_t* src = kCbfWeights.w[(blockIdx.x + blockIdx.y) % kCbfCopies];
-        const bool nz = (unsigned)(t - kCbfW0) < (unsigned)kCbfWords;
+        const int i = min(max(t - kCbfW0, 0), kCbfWords - 1);
+        const bool nz = i == t - kCbfW0;
 #pragma unroll
-        for (int k = 0; k < NK; ++k) wq[k] = nz ? src[k * kCbfWords + t - kCbfW0] : 0u;
+        for (int k = 0; k < NK; ++k) wq[k] = src[k * kCbfWords + i];
+#pragma unroll
+        for (int k = 0; k < NK; ++k) wq[k] = nz ? wq[k] : 0u;
     }
 
-    if (t < nbt) entry_store(t, by0, e0);
-    for (int i = t + NT; i < nbt; i += NT) {
-        int bx, by;
-        entry_pos(i, bx, by);
-        entry_store(i, by, entry_load(bx, by));
+    if (table) {
+        if (t < nbt) entry_store(t, bx0, by0, e0);
+        if (!PLAIN)  // (at most 12 x 8 blocks of 8 px and more: one pass)
+            for (int i = t + NT; i < nbt; i += NT) {
+                int bx, by;
+                entry_pos(i, bx, by);
+                entry_store(i, bx, by, entry_load(bx, by));
+            }
     }
 #pragma unroll
     for (int k = 0; k < NK; ++k) reinterpret_cast<uint32_t*>(wtab)[k * 256 + t] = wq[k];
     if (t < kWtabTail) reinterpret_cast<uint32_t*>(wtab)[NK * 256 + t] = 0;
-    if (t == 0) nwork = 0;
     __syncthreads();
 
     auto store_df = [&](int x0_, int y_, uint32_t df4) {
         const uint32_t o = __umul24(y_ - yb, W) + x0_;
         store_quad_bytes<ALIGNED>(f.df + row0 + o, df4, W - x0_);
-        if (f.out_df) store_quad_bytes<false>(f.out_df + row0 + o, df4, W - x0_);
+        if (out_df) store_quad_bytes<false>(out_df + row0 + o, df4, W - x0_);
     };
 
     // a tile whose windows all lie in non-edge blocks of one region depth is
     // that depth (blocks of 8 px and more: at most 10 x 6 blocks under the
     // windows, one per lane in two steps)
     bool uniform = false;
-    if (!K2 && !f.depth_in && wide && !f.out_d0) {
+    if (!K2 && !depth_in && wide && !out_d0) {
         const int cx = min((max(tx0 - R, 0) >> ks) + (t & 15), min(tx0 + kTileW - 1 + R, W - 1) >> ks) - bx_lo;
         const int b0 = max(ty0 - R, 0) >> ks, b1 = min(ty0 + TH - 1 + R, H - 1) >> ks;
         const uint32_t c = btab[((ty0 >> ks) - by_lo) * bp + (tx0 >> ks) - bx_lo].y;
@@ -442,7 +458,7 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
 #pragma unroll
             for (int half = 0; half < 16 * TH / NT; ++half) {
                 const int x0 = tx0 + 4 * (t & (kTileQ - 1)), y = ty0 + (t >> 4) + NT / 16 * half;
-                if (x0 < W && y < H) store_df(x0, y, c * 0x01010101u);
+                if (x0 < W && y < H) store_df(x0, y, perm(c, c, 0u));
             }
         }
     }
@@ -452,7 +468,7 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
         const int i = t + NT * k;
-        if ((NT * (k + 1) > TR * kTileQuads && i >= TR * kTileQuads) || uniform || H <= 0) break;
+        if ((NT * (k + 1) > TR * kTileQuads && i >= TR * kTileQuads) || uniform || !active) break;
         const int tr = i / kTileQuads, tq = i - tr * kTileQuads;
         const int yo = ty0 - R + tr, xo = tx0 - 4 + 4 * tq;
         const int yy = min(max(yo, 0), H - 1), x0 = min(max(xo, 0), xl);
@@ -464,7 +480,7 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
             if (n < 2) y01 = (y01 & 0xFFFFu) | (kLumaOut << 16);
             y23 = n < 3 ? kLumaOut * 0x10001u : (y23 & 0xFFFFu) | (kLumaOut << 16);
         }
-        if (f.depth_in) {
+        if (depth_in) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) D[j] = (dq[k] >> (8 * j)) & 255u;
         } else {
@@ -476,8 +492,8 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
 #pragma unroll
             for (int j = 1; j < 4; ++j) if (j >= n) D[j] = 0;
         }
-        if (f.out_d0 && yy == yo && x0 == xo && tr >= R && tr < R + TH && tq >= 1 && tq <= kTileQ)
-            store_quad_bytes<false>(f.out_d0 + (size_t)yy * W + x0, D[0] | (D[1] << 8) | (D[2] << 16) | (D[3] << 24), n);
+        if (out_d0 && yy == yo && x0 == xo && tr >= R && tr < R + TH && tq >= 1 && tq <= kTileQ)
+            store_quad_bytes<false>(out_d0 + (size_t)yy * W + x0, D[0] | (D[1] << 8) | (D[2] << 16) | (D[3] << 24), n);
         tY[tr * kRowWords + 2 * tq] = y01;
         tY[tr * kRowWords + 2 * tq + 1] = y23;
         tD[tr * kRowWords + 2 * tq] = D[0] | (D[1] << 16);
@@ -486,7 +502,8 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
     __syncthreads();
 
     const int qx = t & (kTileQ - 1);
-    const int lane = t & 63;
+    const int wave = t >> 6;
+    uint32_t nlist = 0;  // quads in this wave's part of the work list
 #pragma unroll
     for (int half = 0; half < 16 * TH / NT; ++half) {
         const int ty = (t >> 4) + NT / 16 * half;
@@ -504,7 +521,7 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
             // is not uniform and goes to the filter without the pixel test:
             // the block-row steps of the background ramp are most of these)
             uint32_t c = 0, bad = 1, sure = 0;
-            if (!K2 && !f.depth_in && wide) {
+            if (!K2 && !depth_in && wide) {
                 const int bxa = max(x0 - R, 0) >> ks, bxb = min(x0 + 3 + R, W - 1) >> ks;
                 const int bya = max(y - R, 0) >> ks, byb = min(y + R, H - 1) >> ks;
                 const uint2 e00 = btab[16 * (bya - by_lo) + (bxa - bx_lo)], e01 = btab[16 * (bya - by_lo) + (bxb - bx_lo)];
@@ -521,8 +538,8 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
                 const uint32_t splat = c | (c << 16);
 #pragma unroll
                 for (int i = 0; i < S; ++i) {
-                    const int yy = y + i - R;
-                    if (yy < 0 || yy >= H) continue;
+                    // (rows outside the image hold the depths of the nearest
+                    // row inside, which the window holds too)
                     const int base = (ty + i) * kRowWords + 2 * qx;
 #pragma unroll
                     for (int k = (4 - R) >> 1; k <= (7 + R) >> 1; ++k) {
@@ -532,30 +549,33 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
                 }
             }
             if (!bad) {
-                store_df(x0, y, c * 0x01010101u);
+                store_df(x0, y, perm(c, c, 0u));
             } else {
                 needs = true;
             }
         }
-        // compact the quads that need the full filter
+        // compact the quads that need the full filter, each wave into its own
+        // part of the list
         const unsigned long long m = __ballot(needs);
-        if (m) {
-            int base = 0;
-            if (lane == 0) base = atomicAdd(&nwork, __popcll(m));
-            base = __shfl(base, 0);
-            if (needs) work[base + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(t + NT * half);
-        }
+        if (needs) work[kWavePart * wave + nlist + lanes_below(m)] = (uint16_t)(t + NT * half);
+        nlist += (uint32_t)__popcll(m);
     }
+    if ((t & 63) == 0) nwork[wave] = nlist;
     __syncthreads();
     // the full filter: two lanes per listed quad, two pixels each (half the
     // serial length of one lane per quad); the even lane of a pair takes its
-    // partner's two results by a lane shuffle and stores all four
+    // partner's two results by a lane shuffle and stores all four.  All lanes
+    // share the four parts of the list
     constexpr int PW = CbfPairWin<R>::kWords;
-    const int nw2 = 2 * nwork;
+    const int n0 = nwork[0], n1 = n0 + nwork[1], n2 = n1 + nwork[2];
+    const int nw2 = 2 * (n2 + nwork[3]);
     for (int i0 = 0; i0 < nw2; i0 += NT) {
         const int i = i0 + t;
         const bool on = i < nw2;
-        const int q = on ? work[i >> 1] : 0;
+        const int k = i >> 1;
+        const int at = k < n1 ? (k < n0 ? k : k - n0 + kWavePart)
+                              : (k < n2 ? k - n1 + 2 * kWavePart : k - n2 + 3 * kWavePart);
+        const int q = on ? work[at] : 0;
         const int hf = i & 1;
         const int qx_ = q & (kTileQ - 1), ty_ = q / kTileQ;
         const int x0_ = tx0 + 4 * qx_, y_ = ty0 + ty_;

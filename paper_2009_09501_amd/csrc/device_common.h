@@ -123,6 +123,11 @@ __device__ __forceinline__ void store_quad_bytes(uint8_t* p, uint32_t v, int n) 
 // (without it) the slot its component has in the merge's table.
 constexpr uint32_t kResolved = 1u << 31;
 
+// Lanes of the wave below this one whose bit is set in m.
+__device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 constexpr size_t kMaxLds = 160 * 1024;
 
 // The value of v, opaque to the optimiser: indices derived from it are

@@ -94,7 +94,7 @@ __device__ __noinline__ void task_cbf(const FrameDesc* fp, int k, int items, int
     const int item = 4 * k + g;
     const bool active = item < items;
     const int tx = active ? item % gx : 0, ty = active ? item / gx : 0;
-    if (f.K == 2) cbf_tile<R, true, true>(f, tx, ty, t, lds + g * CbfTile<R>::kLdsWords, active);
+    if (f.K == 2) cbf_tile<R, true, CbfKind::kBlocks2>(f, tx, ty, t, lds + g * CbfTile<R>::kLdsWords, active);
     else cbf_tile<R, true>(f, tx, ty, t, lds + g * CbfTile<R>::kLdsWords, active);
 }
 
@@ -270,16 +270,15 @@ __global__ void __launch_bounds__(kRegionThreads) k_mf_merge(const FrameDesc* fr
     else regions_body(f, lds);
 }
 
-// K2: every frame of the batch has blocks of 2 px (the block size is shared).
-template <int R, bool K2>
+template <int R, CbfKind KIND, int TH>
 __global__ void __launch_bounds__(256) k_mf_cbf(const FrameDesc* frames, const int* first, int n) {
-    __shared__ uint32_t lds[CbfTile<R>::kLdsWords];
+    __shared__ uint32_t lds[CbfTile<R, TH>::kLdsWords];
     const int idx = xcd_tile(blockIdx.x, gridDim.x);
     const int fi = frame_of(first, n, idx);
     const FrameDesc f = frames[fi];
     const int local = idx - first[fi];
     const int gx = (f.w + kTileW - 1) / kTileW;
-    cbf_tile<R, true, K2>(f, local % gx, local / gx, threadIdx.x, lds, true);
+    cbf_tile<R, true, KIND, TH>(f, local % gx, local / gx, threadIdx.x, lds, true);
 }
 
 // `rows` consecutive image rows per workgroup, each row's loads issued
@@ -312,6 +311,21 @@ __global__ void __launch_bounds__(1024) k_mf_warp(const FrameDesc* frames, const
 // ---------------------------------------------------------------------------
 // host side
 
+// The block size is the batch's (2 or 4 px) or at least 8 px throughout.
+template <int R, int TH>
+static const void* mf_cbf_fn(int block_size) {
+    return block_size == 2   ? (const void*)&k_mf_cbf<R, CbfKind::kBlocks2, TH>
+           : block_size == 4 ? (const void*)&k_mf_cbf<R, CbfKind::kAny, TH>
+                             : (const void*)&k_mf_cbf<R, CbfKind::kPlain, TH>;
+}
+template <int TH>
+static const void* mf_cbf_fn(int r, int block_size) {
+    return r == 0   ? mf_cbf_fn<0, TH>(block_size)
+           : r == 1 ? mf_cbf_fn<1, TH>(block_size)
+           : r == 2 ? mf_cbf_fn<2, TH>(block_size)
+                    : mf_cbf_fn<3, TH>(block_size);
+}
+
 hipError_t launch_staged(const FrameDesc* d_frames, const int* d_first, const StagedPlan& pl, hipStream_t s) {
     const int n = pl.n;
     const int* first_bs = d_first;
@@ -320,13 +334,9 @@ hipError_t launch_staged(const FrameDesc* d_frames, const int* d_first, const St
     hipLaunchKernelGGL(k_mf_blockstats, dim3(pl.tiles_bs), dim3(256), 0, s, d_frames, first_bs, n, pl.bs_rows);
     if (pl.strips) hipLaunchKernelGGL(k_mf_strip, dim3(pl.strips), dim3(pl.strip_lanes), 0, s, d_frames, first_strip, n);
     hipLaunchKernelGGL(k_mf_merge, dim3(n), dim3(kRegionThreads), pl.merge_lds, s, d_frames);
-    const void* cbf_fn;
-    switch (pl.r) {
-        case 0: cbf_fn = pl.k2 ? (const void*)&k_mf_cbf<0, true> : (const void*)&k_mf_cbf<0, false>; break;
-        case 1: cbf_fn = pl.k2 ? (const void*)&k_mf_cbf<1, true> : (const void*)&k_mf_cbf<1, false>; break;
-        case 2: cbf_fn = pl.k2 ? (const void*)&k_mf_cbf<2, true> : (const void*)&k_mf_cbf<2, false>; break;
-        default: cbf_fn = pl.k2 ? (const void*)&k_mf_cbf<3, true> : (const void*)&k_mf_cbf<3, false>; break;
-    }
+    const void* cbf_fn = pl.cbf_rows == 16   ? mf_cbf_fn<16>(pl.r, pl.block_size)
+                         : pl.cbf_rows == 48 ? mf_cbf_fn<48>(pl.r, pl.block_size)
+                                             : mf_cbf_fn<32>(pl.r, pl.block_size);
     {
         void* args[] = {const_cast<FrameDesc**>(&d_frames), const_cast<int**>(&first_cbf), const_cast<int*>(&n)};
         hipError_t e = hipLaunchKernel(cbf_fn, dim3(pl.tiles_cbf), dim3(256), args, 0, s);
@@ -344,7 +354,7 @@ hipError_t launch_staged(const FrameDesc* d_frames, const int* d_first, const St
     return hipGetLastError();
 }
 
-int batch_tasks(const FrameDesc& f, int phase, int* items, int* gx, int bs_rows) {
+int batch_tasks(const FrameDesc& f, int phase, int* items, int* gx, int bs_rows, int cbf_rows) {
     switch (phase) {
         case 0: {
             const int th = bs_tile_rows_tuned(f.K, bs_rows);
@@ -358,7 +368,7 @@ int batch_tasks(const FrameDesc& f, int phase, int* items, int* gx, int bs_rows)
             return 1;
         case 2:
             *gx = (f.w + kTileW - 1) / kTileW;
-            *items = *gx * ((f.h + kTileH - 1) / kTileH);
+            *items = *gx * ((f.h + cbf_rows - 1) / cbf_rows);
             return (*items + 3) / 4;
         default: {
             int group, quads;

@@ -18,7 +18,7 @@ __device__ __forceinline__ void warp_start_mark(const FrameDesc& f) {
         __hip_atomic_store(f.wmark, f.wmark_value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-template <int R, bool ALIGNED, bool K2, int TH>
+template <int R, bool ALIGNED, CbfKind KIND, int TH>
 __global__ void __launch_bounds__(256) k_cbf(FrameDesc f) {
     __shared__ uint32_t lds[CbfTile<R, TH>::kLdsWords];
     // the start mark of a pipelined call: this kernel runs only once all
@@ -29,7 +29,7 @@ __global__ void __launch_bounds__(256) k_cbf(FrameDesc f) {
     const int gx = gridDim.x;
     const int tile = xcd_tile(blockIdx.y * gx + blockIdx.x, gx * gridDim.y);
     const int ty = tile / gx;
-    cbf_tile<R, ALIGNED, K2, TH>(f, tile - ty * gx, ty, threadIdx.x, lds, true);
+    cbf_tile<R, ALIGNED, KIND, TH>(f, tile - ty * gx, ty, threadIdx.x, lds, true);
 }
 
 // Rows blockIdx.x, blockIdx.x + gridDim.x, ...: a grid of at most a few
@@ -262,28 +262,42 @@ bool warp_shape_cap(int w, int cap, WarpShape* out) {
     return true;
 }
 
+// (an external depth map needs no block lookups, whatever the block size)
+static CbfKind cbf_kind(const FrameDesc& f) {
+    if (f.K == 2 && !f.depth_in) return CbfKind::kBlocks2;
+    return f.K >= 8 && !f.depth_in && !f.out_df && !f.out_d0 ? CbfKind::kPlain : CbfKind::kAny;
+}
+
 template <int R, bool A, int TH>
 static LaunchSpec cbf_th(const FrameDesc& f) {
-    // blocks of 2 px take their raw depth per pixel from global memory (an
-    // external depth map needs no block lookups at all)
-    const void* fn = (f.K == 2 && !f.depth_in) ? reinterpret_cast<const void*>(&k_cbf<R, A, true, TH>)
-                                                 : reinterpret_cast<const void*>(&k_cbf<R, A, false, TH>);
+    const void* fn;
+    switch (cbf_kind(f)) {
+        case CbfKind::kPlain: fn = reinterpret_cast<const void*>(&k_cbf<R, A, CbfKind::kPlain, TH>); break;
+        case CbfKind::kBlocks2: fn = reinterpret_cast<const void*>(&k_cbf<R, A, CbfKind::kBlocks2, TH>); break;
+        default: fn = reinterpret_cast<const void*>(&k_cbf<R, A, CbfKind::kAny, TH>); break;
+    }
     return {fn, dim3((f.w + kTileW - 1) / kTileW, (f.h + TH - 1) / TH), dim3(256), 0};
 }
 
 // Tile height of a filter launch.  Up to about six 32-row tiles per CU (1536;
 // eight are resident) the kernel is one round of workgroups and lasts as long
 // as its slowest tile, so 16-row tiles, half as long, win although they read
-// and convert a quarter more halo; beyond, the halo decides.  Measured, 16
-// against 32 rows: 640x360 7.2 / 9.0 us, 1920x1080 11.7 / 12.3, 2240x1260
-// (1400 tiles) 13.5 / 14.0, 2560x1440 (1800) 15.6 / 15.6, 3200x1800 (2850)
-// 20.2 / 18.6, 3840x2160 26.5 / 23.5.
-constexpr int kShortTiles = 1536;
+// and convert a quarter more halo; with dozens per CU a tile's set-up and halo
+// decide, and 48 rows win although only six fit a CU.  Measured, 16 / 32 / 48
+// rows: 640x360 5.9 / 8.2 / 9.9 us, 1920x1080 10.4 / 10.9 / 12.3, 2240x1260
+// (1400 tiles of 32) 12.0 / 12.8 / 12.6, 2560x1440 (1800) 13.9 / 13.9 / 14.1,
+// 3840x2160 (4080) 24.0 / 21.1 / 21.5, 7680x4320 (16200) 67.0 / 52.6 / 49.6.
+constexpr int kShortTiles = 1536, kTallTiles = 8192;
+
+int cbf_tile_rows(long long tiles32) { return tiles32 <= kShortTiles ? 16 : tiles32 <= kTallTiles ? 32 : 48; }
 
 template <int R, bool A>
 static LaunchSpec cbf_spec(const FrameDesc& f) {
-    const long long tiles = (long long)((f.w + kTileW - 1) / kTileW) * ((f.h + kTileH - 1) / kTileH);
-    return tiles <= kShortTiles ? cbf_th<R, A, 16>(f) : cbf_th<R, A, kTileH>(f);
+    switch (cbf_tile_rows((long long)((f.w + kTileW - 1) / kTileW) * ((f.h + 31) / 32))) {
+        case 16: return cbf_th<R, A, 16>(f);
+        case 48: return cbf_th<R, A, 48>(f);
+        default: return cbf_th<R, A, 32>(f);
+    }
 }
 
 template <bool A>

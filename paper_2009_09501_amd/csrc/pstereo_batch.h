@@ -44,8 +44,9 @@ struct StagedPlan {
     int strips = 0, strip_lanes = 0;  // workgroups of the strip launch and their lanes
     size_t merge_lds = 0;
     int r = 2;
-    bool k2 = false;    // blocks of 2 px (shared by every frame of the batch)
+    int block_size = 0;  // as asked for (0: each frame's own, at least 8 px)
     int warp_rows = 1;  // image rows per warp workgroup
+    int cbf_rows = 32;  // depth-filter tile rows
     int bs_rows = 0;    // block-statistics tile rows (0 = each block size's default)
     int nclass = 0;
     int cls_threads[kMaxWarpClasses];
@@ -76,8 +77,9 @@ JobScratch job_scratch_carve(uint8_t* base, int w, int h, int K);
 // Stage `phase` (0 block statistics, 1 grouping, 2 filter, 3 warp) of frame
 // f: its items (tiles, or rows for the warp) and tile columns, and the
 // fused kernel's tasks for them; bs_rows: the block-statistics tile height
-// (0 = each block size's default, which the fused kernel uses).
-int batch_tasks(const FrameDesc& f, int phase, int* items, int* gx, int bs_rows = 0);
+// (0 = each block size's default, which the fused kernel uses), cbf_rows: the
+// filter's (the fused kernel's: 32).
+int batch_tasks(const FrameDesc& f, int phase, int* items, int* gx, int bs_rows = 0, int cbf_rows = 32);
 bool batch_width_ok(int w);
 hipError_t prepare_batch_kernels();
 hipError_t launch_batch(const BatchDesc& bd, int r, int grid, hipStream_t s);

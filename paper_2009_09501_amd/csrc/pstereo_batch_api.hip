@@ -351,7 +351,7 @@ int batch_prepare_internal(pstereo_batch* b, const pstereo_job* jobs, int n, con
         pl = pstereo::StagedPlan();
         pl.n = n;
         pl.r = p.cbf_radius;
-        pl.k2 = p.block_size == 2;
+        pl.block_size = p.block_size;
         pl.warp_rows = b->tune.warp_rows;
         pl.bs_rows = b->tune.bs_rows;
         int* fb = b->h_first;
@@ -359,6 +359,13 @@ int batch_prepare_internal(pstereo_batch* b, const pstereo_job* jobs, int n, con
         int* fs = b->h_first + 2 * (n + 1);
         int nb_max = 1;
         std::vector<int> cls(n);
+        long long tiles32 = 0;
+        for (int i = 0; i < n; ++i) {
+            int items, gx;
+            (void)pstereo::batch_tasks(b->h_frames[i], 2, &items, &gx);
+            tiles32 += items;
+        }
+        pl.cbf_rows = pstereo::cbf_tile_rows(tiles32);
         for (int i = 0; i < n; ++i) {
             const FrameDesc& f = b->h_frames[i];
             int items, gx;
@@ -366,7 +373,7 @@ int batch_prepare_internal(pstereo_batch* b, const pstereo_job* jobs, int n, con
             (void)pstereo::batch_tasks(f, 0, &items, &gx, pl.bs_rows);  // block-statistics tiles
             pl.tiles_bs += items;
             fc[i] = pl.tiles_cbf;
-            (void)pstereo::batch_tasks(f, 2, &items, &gx);  // depth-filter tiles
+            (void)pstereo::batch_tasks(f, 2, &items, &gx, 0, pl.cbf_rows);  // depth-filter tiles
             pl.tiles_cbf += items;
             fs[i] = pl.strips;
             if (f.rstrip > 0) {

@@ -88,6 +88,7 @@ LaunchSpec spec_rg_strip(const FrameDesc& f);
 LaunchSpec spec_rg_merge(const FrameDesc& f);
 LaunchSpec spec_rg_final(const FrameDesc& f);
 LaunchSpec spec_cbf(const FrameDesc& f);
+int cbf_tile_rows(long long tiles32);  // from the number of 64 x 32 tiles
 LaunchSpec spec_warp(const FrameDesc& f, const WarpShape& ws);
 // Block-iterative inpainting: reset (before the warp), the sweeps in launches
 // of kInpaintSweeps, composition once launch `last` has filled nothing in its

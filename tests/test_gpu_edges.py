@@ -51,11 +51,13 @@ def test_rows_off_the_dword_grid(ctx, w, h, off):
 
 @pytest.mark.parametrize("w,h,K,r", [(64, 16, 8, 2), (65, 17, 8, 2), (63, 15, 4, 3), (68, 18, 4, 3), (128, 33, 8, 3),
                                      (132, 31, 16, 1), (60, 48, 32, 2), (196, 50, 64, 3), (127, 64, 8, 0),
-                                     (4096, 768, 0, 2), (4096, 769, 0, 2), (4094, 769, 0, 3)])
+                                     (4096, 768, 0, 2), (4096, 769, 0, 2), (4094, 769, 0, 3),
+                                     (4096, 4096, 0, 2), (4095, 4097, 0, 1)])
 def test_filter_tile_edges(ctx, oracle_mod, w, h, K, r):
     """Filter tiles cut by the frame's edges at every radius, and the largest
-    frame of 16-row tiles beside the smallest of 32-row ones: filtered depth
-    and views."""
+    frames of 16-row and 32-row tiles beside the smallest of 32-row and 48-row
+    ones: views, and the filtered depth of the small ones (a dump takes the
+    general kernel, so the views are from a call without one)."""
     from paper_2009_09501_amd import pstereo_params_init, pstereo_synthesize
     dev = torch.device("cuda:0")
     host = synth.gen_frame(700 + w + h + r, w, h, 12, 4.0)
@@ -63,10 +65,11 @@ def test_filter_tile_edges(ctx, oracle_mod, w, h, K, r):
     outs = [torch.empty_like(f) for _ in range(3)]
     df = torch.empty((h, w), dtype=torch.uint8, device=dev)
     B = min(20, w)
-    p = pstereo_params_init(max_disparity=B, block_size=K, cbf_radius=r, out_depth=df)
-    p.stream = torch.cuda.current_stream().cuda_stream
     print(f"filter tiles: {w}x{h} K={K} r={r}", flush=True)
-    pstereo_synthesize(ctx.handle, f, w, h, p, *outs)
+    for dump in (df, None):
+        p = pstereo_params_init(max_disparity=B, block_size=K, cbf_radius=r, out_depth=dump)
+        p.stream = torch.cuda.current_stream().cuda_stream
+        pstereo_synthesize(ctx.handle, f, w, h, p, *outs)
     torch.cuda.synchronize()
     refs.assert_views(outs, refs.views(("tiles", w, h, K, r), host, B, K=K, r=r), f"{w}x{h} K={K} r={r}")
     if w * h < 1 << 17:
