@@ -267,6 +267,7 @@ __global__ void __launch_bounds__(kRegionThreads) k_mf_merge(const FrameDesc* fr
     extern __shared__ uint32_t lds[];
     const FrameDesc f = frames[blockIdx.x];
     if (f.rstrip > 0) rg_merge_body(f, lds);
+    else if (f.gw * f.gh <= kSmallBlocks) rg_small_body(f, lds);
     else regions_body(f, lds);
 }
 

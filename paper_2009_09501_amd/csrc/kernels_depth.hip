@@ -39,6 +39,12 @@ __global__ void __launch_bounds__(kRegionThreads) k_regions(FrameDesc f) {
     signal_done(f);
 }
 
+__global__ void __launch_bounds__(kStripLanes) k_rg_small(FrameDesc f) {
+    extern __shared__ uint32_t lds[];
+    rg_small_body(f, lds);
+    signal_done(f);
+}
+
 __global__ void __launch_bounds__(kStripLanes) k_rg_strip(FrameDesc f) {
     __shared__ uint32_t lds[rg_strip_lds_words()];
     rg_strip_body(f, blockIdx.x, blockDim.x, lds);
@@ -116,18 +122,22 @@ LaunchSpec spec_blockstats(const FrameDesc& f) { return f.aligned ? bs_k<true>(f
 
 size_t regions_lds_bytes(int nb) { return regions_lds_bytes_c(nb); }
 size_t merge_lds_bytes(int nb) { return std::max(rg_merge_lds_words() * 4, regions_lds_bytes_c(nb)); }
+static_assert(rg_small_lds_words() <= rg_merge_lds_words(), "a batch groups a small grid in the merge's LDS");
 
 LaunchSpec spec_regions(const FrameDesc& f) {
+    if (f.gw * f.gh <= kSmallBlocks)
+        return {reinterpret_cast<const void*>(&k_rg_small), dim3(1), dim3(kStripLanes), rg_small_lds_words() * 4};
     return {reinterpret_cast<const void*>(&k_regions), dim3(1), dim3(kRegionThreads), regions_lds_bytes(f.gw * f.gh)};
 }
 
 // Rows per strip: about one block per lane (two for rows wider than the
-// workgroup), 0 when a row does not fit a strip.  Narrow grids take strips of
-// six rows (unless that makes more than kMaxStrips): the unions inside a strip
-// walk its rows one after the other, which joining more strips does not
-// (640x360: 12-row strips 27.5 us a frame, six 26.5, two 26.8).
+// workgroup), 0 when a row does not fit a strip or one workgroup groups the
+// whole grid.  Narrow grids take strips of six rows (unless that makes more
+// than kMaxStrips): the unions inside a strip walk its rows one after the
+// other, which joining more strips does not (80x45 blocks: 12-row strips
+// 27.5 us a frame, six 26.5, two 26.8).
 int strip_rows(int gw, int gh) {
-    if (gw < 1 || gw > kStripBlocks) return 0;
+    if (gw < 1 || gw > kStripBlocks || gw * gh <= kSmallBlocks) return 0;
     if (gw > kStripLanes) return 1;
     return std::min(kStripLanes / gw, std::max(6, (gh + kMaxStrips - 1) / kMaxStrips));
 }
@@ -165,6 +175,9 @@ hipError_t prepare_depth_kernels() {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_regions),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds);
     if (e != hipSuccess) return e;
+    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_rg_small),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds)) != hipSuccess)
+        return e;
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_rg_merge), hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)kMaxLds);
 }

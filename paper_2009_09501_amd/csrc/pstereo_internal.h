@@ -81,6 +81,7 @@ LaunchSpec spec_regions(const FrameDesc& f);
 int strip_rows(int gw, int gh);
 int strip_lanes(int gw, int rows);
 constexpr int kRegionSlots = 4096;  // slots the merge holds in LDS
+constexpr int kSmallBlocks = 4096;  // blocks of a grid grouped whole on one workgroup (k_rg_small)
 constexpr int kMaxStrips = 64;      // a strip but the last holds more than 512 blocks
 constexpr int kStripHdrBits = 2;    // header word of the first join bits (2048 columns: 64 words)
 constexpr int kStripHdrWords = 66;

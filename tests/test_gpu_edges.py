@@ -92,12 +92,16 @@ def _comb(gw, gh, K, every):
                                         ("still", 170, 190), ("still", 171, 190), ("still", 80, 45),
                                         ("still", 1, 2100), ("still", 64, 1), ("still", 2049, 15),
                                         ("comb", 512, 64), ("comb", 341, 90), ("comb", 100, 60),
-                                        ("stripes", 1500, 20), ("stripes", 60, 66), ("stripes", 66, 68)])
+                                        ("stripes", 1500, 20), ("stripes", 60, 66), ("stripes", 66, 68),
+                                        ("still", 64, 64), ("comb", 64, 64), ("stripes", 64, 64), ("still", 4096, 1),
+                                        ("still", 1, 4096), ("still", 241, 17), ("still", 4097, 1), ("still", 1, 1),
+                                        ("comb", 63, 65), ("still", 1024, 4), ("still", 1025, 3)])
 def test_grouping_strips(oracle_mod, kind, gw, gh):
     """Grids of 2 px blocks at the strips' limits (rows wider than a
-    workgroup, one and many rows a strip, 63 strips), regions that join along
-    many columns, and more components than the merge holds: region labels,
-    depths and raw depth."""
+    workgroup, one and many rows a strip, 63 strips), of the size up to which
+    one workgroup groups the whole grid and one block more, regions that join
+    along many columns, and more components than the merge holds: region
+    labels, depths and raw depth."""
     from paper_2009_09501_amd import Context, pstereo_debug_blocks
     K, w, h = 2, 2 * gw, 2 * gh
     if kind == "still":
