@@ -633,7 +633,7 @@ __host__ __device__ constexpr size_t regions_lds_bytes_c(int nb) {
 //     the smallest), sums counts and takes the lowest row per merged
 //     component, picks the background and replaces each slot's list entry by
 //     its final label and depth.  With more than kRegionSlots slots (or
-//     kJoinSlots joins) it runs regions_body instead, for the whole frame;
+//     kJoinSlots joins) it runs regions_loops instead, for the whole frame;
 //   final (only for the per-block dump): one lane per block turns its slot
 //     into the final label and depth.  The depth filter resolves the depths
 //     it needs from the slot list itself.
@@ -859,6 +859,135 @@ __host__ __device__ constexpr size_t rg_merge_lds_words() {
     return 5 * (size_t)kRegionSlots + kJoinSlots + kMaxStrips + 4;
 }
 
+// Region grouping of a whole frame on one 1024-lane workgroup in plain loops
+// over its blocks, for launches that rarely come to it (more components than
+// the merge holds): the same components, labels and depths as regions_body,
+// whose 32 blocks a lane in registers set the registers of the kernel around
+// it.  With that body the merge took 128 VGPRs, 21 more spilled, and with
+// it as a function called from there 540 bytes of scratch a lane; with this
+// one 64 and none: 3840x2160 66.0 (67.5 called) -> 64.7 us a frame, 1920x1080
+// 38.2 (39.9) -> 37.3.  A checkerboard of 240 x 135 blocks, which does come
+// here, 87.8 -> 85.0; random blocks of 1024x128 px with half of them linked,
+// 160.7 -> 167.5.  lds: gw * gh + 1 words.
+__device__ __forceinline__ void regions_loops(const FrameDesc& f, uint32_t* lds) {
+    const int gw = f.gw, gh = f.gh, nb = gw * gh;
+    const int t = threadIdx.x, lane = t & 63;
+    uint32_t* par = lds;
+    uint32_t* misc = par + nb;  // [0]: background key
+    const uint32_t gwm = gw > 1 ? (uint32_t)((0x100000000ull + (uint32_t)gw - 1) / (uint32_t)gw) : 0u;
+    auto row_of = [&](int b) { return (int)div_u16((uint32_t)b, gwm, (uint32_t)gw); };
+    if (t == 0) misc[0] = 0;
+    // kU blocks of each lane at a time, so that their loads are in flight
+    // together
+    constexpr int kU = 8, kStep = kU * kRegionThreads;
+    const int last = nb - 1;
+    // each block under the start of its run of the row in the wave's 64
+    // blocks, or under the block before them
+    for (int o = t; o - t < nb; o += kStep) {
+        uint32_t s[kU], left[kU];
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            const int b = min(o + k * kRegionThreads, last);
+            s[k] = f.stats[b];
+            left[k] = f.stats[max(b - 1, 0)];
+        }
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            const int b = o + k * kRegionThreads;
+            const bool runs = b < nb && b != row_of(min(b, last)) * gw && linked(left[k], s[k], f.tau);
+            const unsigned long long m = ~__ballot(runs) & (((1ull << lane) << 1) - 1ull);
+            if (b < nb) par[b] = (uint32_t)(m ? b - lane + 63 - __clzll((long long)m) : b - lane - 1);
+        }
+    }
+    __syncthreads();
+    // links down, but for those that the blocks to the left have joined
+    for (int o = t; o + gw < nb; o += kStep) {
+        uint32_t s[kU], left[kU], below[kU], bl[kU];
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            const int b = min(o + k * kRegionThreads, last - gw);
+            const int l = max(b - 1, 0);
+            s[k] = f.stats[b];
+            left[k] = f.stats[l];
+            below[k] = f.stats[b + gw];
+            bl[k] = f.stats[l + gw];
+        }
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            const int b = o + k * kRegionThreads;
+            if (b + gw >= nb || !linked(s[k], below[k], f.tau)) continue;
+            if (b != row_of(b) * gw && linked(left[k], s[k], f.tau) && linked(bl[k], below[k], f.tau) &&
+                linked(left[k], bl[k], f.tau))
+                continue;
+            ufl_unite(par, (uint32_t)b, (uint32_t)(b + gw));
+        }
+    }
+    __syncthreads();
+    for (int b = t; b < nb; b += kRegionThreads) f.labels[b] = (int32_t)ufl_find(par, (uint32_t)b);
+    __syncthreads();
+    for (int b = t; b < nb; b += kRegionThreads) par[b] = 0;
+    __syncthreads();
+    // per non-edge label the lowest row + 1 (low half), then the block count
+    // (high half), by pieces of a row
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int o = t; o - t < nb; o += kStep) {
+            uint32_t s[kU], root[kU];
+#pragma unroll
+            for (int k = 0; k < kU; ++k) {
+                const int b = o + k * kRegionThreads;
+                s[k] = b < nb ? f.stats[b] : 1u << 24;
+                root[k] = b < nb ? (uint32_t)f.labels[b] : 0xFFFFFFFFu;
+            }
+#pragma unroll
+            for (int k = 0; k < kU; ++k) {
+                const int b = min(o + k * kRegionThreads, last);
+                const bool ne = !(s[k] >> 24);
+                const int y = row_of(b);
+                const uint32_t left = (uint32_t)__shfl_up((int)root[k], 1);
+                const bool head = ne && (lane == 0 || b == y * gw || left != root[k]);
+                const unsigned long long stop = __ballot(head) | ~__ballot(ne);
+                if (head) {
+                    const unsigned long long m = lane < 63 ? stop >> (lane + 1) : 0ull;
+                    const uint32_t len = m ? (uint32_t)__ffsll((long long)m) : 64u - (uint32_t)lane;
+                    if (pass == 0) atomicMax(&par[root[k]], (uint32_t)y + 1u);
+                    else atomicAdd(&par[root[k]], len << 16);
+                }
+            }
+        }
+        __syncthreads();
+    }
+    // background = the largest non-edge component, ties to the smaller label;
+    // each non-edge label's word becomes its depth
+    uint32_t best = 0;
+    for (int b = t; b < nb; b += kRegionThreads) {
+        const uint32_t w = par[b];  // 0: not a non-edge label
+        if (!w) continue;
+        best = max(best, (w & 0xFFFF0000u) | (0xFFFFu - (uint32_t)b));
+        par[b] = (uint32_t)ramp((int)(w & 0xFFFFu) - 1, gh);
+    }
+    best = wave_scan_max(best);
+    if (lane == 63 && best) atomicMax(&misc[0], best);
+    __syncthreads();
+    const uint32_t bg = 0xFFFFu - (misc[0] & 0xFFFFu);
+    for (int o = t; o < nb; o += kStep) {
+        uint32_t s[kU], root[kU];
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            const int b = min(o + k * kRegionThreads, last);
+            s[k] = f.stats[b];
+            root[k] = (uint32_t)f.labels[b];
+        }
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            const int b = o + k * kRegionThreads;
+            if (b >= nb) break;
+            const uint32_t dep = !(s[k] >> 24) && root[k] != bg ? par[root[k]] : (uint32_t)ramp(row_of(b), gh);
+            f.binfo[b] = make_uint2(s[k], dep | kResolved);
+        }
+    }
+}
+
+
 __device__ __forceinline__ void rg_merge_body(const FrameDesc& f, uint32_t* lds) {
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int gw = f.gw, gh = f.gh, SR = f.rstrip;
@@ -913,7 +1042,7 @@ __device__ __forceinline__ void rg_merge_body(const FrameDesc& f, uint32_t* lds)
     if (ns > kRegionSlots || njoins > kJoinSlots) {
         // too many strip-local components: group the whole frame here
         __syncthreads();  // the list is written over
-        regions_body(f, lds);
+        regions_loops(f, lds);
         return;
     }
     if (t < kMaxStrips) first[t] = before - (uint32_t)(t * per);

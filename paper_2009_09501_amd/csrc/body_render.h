@@ -3,8 +3,8 @@
 //
 //   k_cbf   pixel depth (from the block tables) and its cross-bilateral
 //           filter guided by luma (Section 3: filtered depth map; Section 4:
-//           GPU cross-bilateral filtering), on 64 x 32 or 64 x 16 pixel
-//           tiles with a halo in LDS.  Windows whose depths are all equal take the exact
+//           GPU cross-bilateral filtering), on 64 x 16, 64 x 32 or 64 x 48
+//           pixel tiles with a halo in LDS.  Windows whose depths are all equal take the exact
 //           shortcut; the other quads are compacted into a workgroup list so
 //           that only they pay for the weighted sum.  Output: filtered depth,
 //           one byte per pixel, in a scratch buffer.
@@ -215,7 +215,7 @@ __device__ __forceinline__ void quad_depth_k2(const FrameDesc& f, int x0, int yy
 }
 
 // ---------------------------------------------------------------------------
-// k_cbf: 64 x TH pixel tiles (TH = 32, or 16 for small frames), 256 lanes;
+// k_cbf: 64 x TH pixel tiles (TH = 16, 32 or 48 by the launch's size), 256 lanes;
 // lane = one quad in every 16th tile row.  LDS holds, for the tile and a
 // 4 px / R row halo, doubled luma and raw depth as u16 pairs (two dwords per
 // quad).  A window of quad x0 reads the six dwords of columns x0-4 .. x0+7 per

@@ -268,7 +268,7 @@ __global__ void __launch_bounds__(kRegionThreads) k_mf_merge(const FrameDesc* fr
     const FrameDesc f = frames[blockIdx.x];
     if (f.rstrip > 0) rg_merge_body(f, lds);
     else if (f.gw * f.gh <= kSmallBlocks) rg_small_body(f, lds);
-    else regions_body(f, lds);
+    else regions_loops(f, lds);
 }
 
 template <int R, CbfKind KIND, int TH>

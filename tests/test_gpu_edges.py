@@ -124,6 +124,24 @@ def test_grouping_strips(oracle_mod, kind, gw, gh):
         ctx.close()
 
 
+@pytest.mark.parametrize("kind", ["still", "comb"])
+def test_grouping_in_a_batch(ctx, kind):
+    """A batch whose frames take each form of the grouping: one workgroup,
+    strips, rows too wide for a strip, and (the comb of 512 x 64 blocks) more
+    components than the merge holds."""
+    from paper_2009_09501_amd import pstereo_params_init
+    from paper_2009_09501_amd.pstereo import PSTEREO_SYNC, make_jobs, pstereo_synthesize_batch
+    grids = [(64, 64), (512, 64), (2050, 4), (100, 60), (4, 1)]
+    host = [synth.gen_frame(gw, 2 * gw, 2 * gh, 14, 3.0) if kind == "still" else _comb(gw, gh, 2, 2) for gw, gh in grids]
+    frames = [torch.from_numpy(x).to("cuda:0") for x in host]
+    outs = [[torch.zeros_like(f) for _ in range(3)] for f in frames]
+    print(f"batch grouping {kind}", flush=True)
+    p = pstereo_params_init(block_size=2, flags=PSTEREO_SYNC)
+    pstereo_synthesize_batch(ctx.handle, make_jobs(frames, outs, [8] * len(frames)), len(frames), p)
+    for x, o, g in zip(host, outs, grids):
+        refs.assert_views(o, refs.views(("batch grouping", kind, *g), x, 8, K=2), f"batch grouping {kind} {g}")
+
+
 @pytest.mark.parametrize("w,h,B", [(64, 32, 60), (65, 33, 60), (200, 97, 120), (129, 64, 255), (1, 40, 4), (640, 40, 255)])
 def test_inpaint_wide_holes(ctx, oracle_mod, w, h, B):
     """Holes wider than a tile and its halo, tiles cut by the frame's edges:
