@@ -632,8 +632,8 @@ __host__ __device__ constexpr size_t regions_lds_bytes_c(int nb) {
 //     the slots numbered strip by strip, so in label order, again rooted at
 //     the smallest), sums counts and takes the lowest row per merged
 //     component, picks the background and replaces each slot's list entry by
-//     its final label and depth.  With more than kRegionSlots slots (or
-//     kJoinSlots joins) it runs regions_loops instead, for the whole frame;
+//     its final label and depth.  With more than kRegionSlots slots it runs
+//     regions_loops instead, for the whole frame;
 //   final (only for the per-block dump): one lane per block turns its slot
 //     into the final label and depth.  The depth filter resolves the depths
 //     it needs from the slot list itself.
@@ -854,9 +854,13 @@ __device__ __forceinline__ void rg_strip_body(const FrameDesc& f, int strip, int
     }
 }
 
-constexpr int kJoinSlots = 8192;  // joins the merge lists in LDS
-__host__ __device__ constexpr size_t rg_merge_lds_words() {
-    return 5 * (size_t)kRegionSlots + kJoinSlots + kMaxStrips + 4;
+// LDS of the merge of a grid of nb blocks: its tables, then the joins, 16 bits
+// each and at most one a block, so that every grid's fit.  (Past a list of 8192
+// the frame went to one workgroup as a whole: 512x64 blocks with 32 slots and
+// 15,872 joins 127 -> 62 us a frame, 1000x32 with 15,500 131 -> 64.)
+static_assert(PSTEREO_MAX_BLOCKS <= 1 << 16 && kRegionSlots <= 1 << 16, "block and slot indices of 16 bits");
+__host__ __device__ constexpr size_t rg_merge_lds_words(int nb) {
+    return 4 * (size_t)kRegionSlots + kMaxStrips + 4 + (size_t)(nb + 1) / 2;
 }
 
 // Region grouping of a whole frame on one 1024-lane workgroup in plain loops
@@ -993,13 +997,12 @@ __device__ __forceinline__ void rg_merge_body(const FrameDesc& f, uint32_t* lds)
     const int gw = f.gw, gh = f.gh, SR = f.rstrip;
     const int nstrip = (gh + SR - 1) / SR, per = SR * gw;  // blocks per strip
     uint32_t* par = lds;
-    uint32_t* lab = par + kRegionSlots;   // label of a strip-local component
-    uint32_t* at = lab + kRegionSlots;    // its place in the slot list
-    uint32_t* cnt = at + kRegionSlots;
+    uint32_t* lab = par + kRegionSlots;   // label of a strip-local component | its place in the slot list << 16
+    uint32_t* cnt = lab + kRegionSlots;
     uint32_t* row = cnt + kRegionSlots;
-    uint32_t* joins = row + kRegionSlots;   // blocks that join the strip above theirs
-    uint32_t* first = joins + kJoinSlots;   // per strip: its first slot - the place of that in the list
+    uint32_t* first = row + kRegionSlots;   // per strip: its first slot - the place of that in the list
     uint32_t* misc = first + kMaxStrips;    // [0]: background key
+    uint16_t* joins = reinterpret_cast<uint16_t*>(misc + 4);  // blocks that join the strip above theirs
 
     // A wave takes strips wave, wave + 16, ..., and the rows they start with in
     // pieces of 64 columns (lane l knows the l-th: at most 4 strips x 9 pieces,
@@ -1032,14 +1035,13 @@ __device__ __forceinline__ void rg_merge_body(const FrameDesc& f, uint32_t* lds)
         const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(bits >> 32), q);
         const unsigned long long m = ((unsigned long long)hi << 32) | lo;
         const uint32_t o = __builtin_amdgcn_readlane(jpos, q) + lanes_below(m);
-        if (((m >> lane) & 1ull) && o < (uint32_t)kJoinSlots)
-            joins[o] = (uint32_t)__builtin_amdgcn_readlane(pblk, q) + (uint32_t)lane;
+        if ((m >> lane) & 1ull) joins[o] = (uint16_t)(__builtin_amdgcn_readlane(pblk, q) + (uint32_t)lane);
     }
     // slot numbers: strip s's slots follow those of the strips above it
     const uint32_t incl = wave_scan_add(own);
     const uint32_t before = incl - own;
     const int ns = (int)__builtin_amdgcn_readlane(incl, 63);
-    if (ns > kRegionSlots || njoins > kJoinSlots) {
+    if (ns > kRegionSlots) {
         // too many strip-local components: group the whole frame here
         __syncthreads();  // the list is written over
         regions_loops(f, lds);
@@ -1055,8 +1057,7 @@ __device__ __forceinline__ void rg_merge_body(const FrameDesc& f, uint32_t* lds)
         for (uint32_t p = lane; p < c; p += 64) {
             const uint32_t e = p < 64 ? ent[i] : f.rlist[s * per + p];
             par[o + p] = o + p;
-            lab[o + p] = (uint32_t)(s * per) + (e & 2047u);
-            at[o + p] = (uint32_t)(s * per) + p;
+            lab[o + p] = ((uint32_t)(s * per) + (e & 2047u)) | (((uint32_t)(s * per) + p) << 16);
             cnt[o + p] = ((e >> 11) & 2047u) + 1u;
             row[o + p] = (uint32_t)(s * SR) + (e >> 22);
         }
@@ -1094,9 +1095,18 @@ __device__ __forceinline__ void rg_merge_body(const FrameDesc& f, uint32_t* lds)
     }
     __syncthreads();
     if (t < njoins) ufl_unite(par, ja, jb);
-    for (int i = t + kStripLanes; i < njoins; i += kStripLanes) {
-        join_slots(joins[i], ja, jb);
-        ufl_unite(par, ja, jb);
+    // a lane's joins past the first, four at a time, so that their loads are
+    // in flight together; of a row of joins between the same two slots only
+    // the first is left
+    for (int o = t + kStripLanes; o < njoins; o += 4 * kStripLanes) {
+        uint32_t a[4], b[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) join_slots(joins[min(o + u * kStripLanes, njoins - 1)], a[u], b[u]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t pair = (a[u] << 16) | b[u], left = (uint32_t)__shfl_up((int)pair, 1);
+            if (lane == 0 || left != pair) ufl_unite(par, a[u], b[u]);
+        }
     }
     __syncthreads();
 
@@ -1131,7 +1141,7 @@ __device__ __forceinline__ void rg_merge_body(const FrameDesc& f, uint32_t* lds)
         const int s = t + i * kStripLanes;
         if (s >= ns) break;
         const uint32_t r = root[i];
-        f.rlist[at[s]] = (lab[r] << 9) | ((r == bg ? 1u : 0u) << 8) | (uint32_t)ramp((int)row[r], gh);
+        f.rlist[lab[s] >> 16] = ((lab[r] & 0xFFFFu) << 9) | ((r == bg ? 1u : 0u) << 8) | (uint32_t)ramp((int)row[r], gh);
     }
 }
 

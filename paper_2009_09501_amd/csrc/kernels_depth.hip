@@ -121,8 +121,9 @@ static LaunchSpec bs_k(const FrameDesc& f) {
 LaunchSpec spec_blockstats(const FrameDesc& f) { return f.aligned ? bs_k<true>(f) : bs_k<false>(f); }
 
 size_t regions_lds_bytes(int nb) { return regions_lds_bytes_c(nb); }
-size_t merge_lds_bytes(int nb) { return std::max(rg_merge_lds_words() * 4, regions_lds_bytes_c(nb)); }
-static_assert(rg_small_lds_words() <= rg_merge_lds_words(), "a batch groups a small grid in the merge's LDS");
+size_t merge_lds_bytes(int nb) {
+    return std::max(std::max(rg_merge_lds_words(nb), rg_small_lds_words()) * 4, regions_lds_bytes_c(nb));
+}
 
 LaunchSpec spec_regions(const FrameDesc& f) {
     if (f.gw * f.gh <= kSmallBlocks)

@@ -192,3 +192,80 @@ def test_inpaint_last_allowed_sweep(ctx, oracle_mod, h):
     ref = oracle_mod.synthesize(host, 255, T=-1, r=0, depth=depth)
     want, _ = oracle_mod.inpaint_blocks(host, ref.warpL)
     assert np.array_equal(outs[0].cpu().numpy(), want)
+
+
+def _joins(gw, gh, K, tooth):
+    """Rows of one colour above rows that link up in every column
+    (``tooth`` 15: single blocks that do not link to each other) or in every
+    second one (``tooth`` 24: rows of linked blocks, every second one too far
+    from the row above): few components, many joins between strips."""
+    img = np.full((gh, gw, 3), 100, np.uint8)
+    img[1::2, 0::2, 0] = 100 - 15 if tooth == 15 else 100 + 12
+    img[1::2, 1::2, 0] = 100 + 15 if tooth == 15 else 100 + 36
+    return np.kron(img, np.ones((K, K, 1), np.uint8))
+
+
+@pytest.mark.parametrize("gw,gh,tooth", [(512, 64, 15), (340, 96, 15), (341, 96, 15), (1000, 32, 24), (2047, 16, 24),
+                                         (513, 63, 24)])
+def test_grouping_many_joins(oracle_mod, gw, gh, tooth):
+    """Few components and up to 15,000 joins across the strips' boundaries
+    (one, two or three rows a strip): labels, region depths and raw depth."""
+    from paper_2009_09501_amd import Context, pstereo_debug_blocks
+    K, w, h = 2, 2 * gw, 2 * gh
+    host = _joins(gw, gh, K, tooth)
+    dev = torch.device("cuda:0")
+    ctx = Context(0, w, h)
+    try:
+        print(f"many joins {gw}x{gh} blocks tooth {tooth}", flush=True)
+        raw = torch.empty((h, w), dtype=torch.uint8, device=dev)
+        ctx.synthesize(torch.from_numpy(host).to(dev), max_disparity=2, block_size=K, cbf_radius=0, out_depth_raw=raw)
+        torch.cuda.synchronize()
+        ref = oracle_mod.synthesize(host, 2, K=K, r=0)
+        _, labels, dblk = pstereo_debug_blocks(ctx.handle)
+        assert np.array_equal(labels, ref.labels.reshape(gh, gw))
+        assert np.array_equal(dblk, ref.dblk.reshape(gh, gw))
+        assert np.array_equal(raw.cpu().numpy(), ref.D0)
+    finally:
+        ctx.close()
+
+
+def test_grouping_many_joins_stays_in_the_merge():
+    """A frame of few components is merged from its strips however many joins
+    they have, not grouped as a whole by one workgroup: its grouping takes
+    well under the time of a frame whose components overflow the merge."""
+    from paper_2009_09501_amd import Context, pstereo_params_init, pstereo_profile_collect, pstereo_synthesize
+    from paper_2009_09501_amd.pstereo import PSTEREO_PROFILE
+    gw, gh, w, h = 512, 64, 1024, 128
+    us = []
+    ctx = Context(0, w, h)
+    try:
+        for host in (_joins(gw, gh, 2, 15), _comb(gw, gh, 2, 2)):
+            f = torch.from_numpy(host).to("cuda:0")
+            outs = [torch.empty_like(f) for _ in range(3)]
+            p = pstereo_params_init(block_size=2, flags=PSTEREO_PROFILE)
+            p.stream = torch.cuda.current_stream().cuda_stream
+            for _ in range(2):  # the second collection is without first uses
+                for _ in range(50):
+                    pstereo_synthesize(ctx.handle, f, w, h, p, *outs)
+                torch.cuda.synchronize()
+                ms, n, _ = pstereo_profile_collect(ctx.handle)
+            us.append(ms[1] / n * 1e3)
+    finally:
+        ctx.close()
+    print(f"grouping of many joins {us[0]:.1f} us, of an overflow {us[1]:.1f} us", flush=True)
+    assert us[0] < 0.6 * us[1]
+
+
+def test_grouping_many_joins_in_a_batch(ctx):
+    """The same frames in one batch."""
+    from paper_2009_09501_amd import pstereo_params_init
+    from paper_2009_09501_amd.pstereo import PSTEREO_SYNC, make_jobs, pstereo_synthesize_batch
+    grids = [(512, 64, 15), (340, 96, 15), (1000, 32, 24), (2046, 16, 24)]
+    host = [_joins(gw, gh, 2, tooth) for gw, gh, tooth in grids]
+    frames = [torch.from_numpy(x).to("cuda:0") for x in host]
+    outs = [[torch.zeros_like(f) for _ in range(3)] for f in frames]
+    print("batch of many joins", flush=True)
+    p = pstereo_params_init(block_size=2, flags=PSTEREO_SYNC)
+    pstereo_synthesize_batch(ctx.handle, make_jobs(frames, outs, [8] * len(frames)), len(frames), p)
+    for x, o, g in zip(host, outs, grids):
+        refs.assert_views(o, refs.views(("many joins", *g), x, 8, K=2), f"batch of many joins {g}")
