@@ -863,16 +863,19 @@ __host__ __device__ constexpr size_t rg_merge_lds_words(int nb) {
     return 4 * (size_t)kRegionSlots + kMaxStrips + 4 + (size_t)(nb + 1) / 2;
 }
 
-// Region grouping of a whole frame on one 1024-lane workgroup in plain loops
-// over its blocks, for launches that rarely come to it (more components than
-// the merge holds): the same components, labels and depths as regions_body,
-// whose 32 blocks a lane in registers set the registers of the kernel around
-// it.  With that body the merge took 128 VGPRs, 21 more spilled, and with
-// it as a function called from there 540 bytes of scratch a lane; with this
-// one 64 and none: 3840x2160 66.0 (67.5 called) -> 64.7 us a frame, 1920x1080
-// 38.2 (39.9) -> 37.3.  A checkerboard of 240 x 135 blocks, which does come
-// here, 87.8 -> 85.0; random blocks of 1024x128 px with half of them linked,
-// 160.7 -> 167.5.  lds: gw * gh + 1 words.
+// Region grouping of a whole frame on one 1024-lane workgroup in loops over
+// its blocks, for launches that rarely come to it (more components than the
+// merge holds): the same components, labels and depths as regions_body, whose
+// 32 blocks a lane in registers set the registers of the kernel around it.
+// With that body the merge took 128 VGPRs, 21 more spilled, and with it as a
+// function called from there 540 bytes of scratch a lane; with this one 70 and
+// none: 3840x2160 66.0 (67.5 called) -> 64.7 us a frame, 1920x1080 38.2 (39.9)
+// -> 37.3.  Runs are joined by hooks and shortened paths, twice, before any
+// search, and labels stay in registers, two to each (region grouping of a
+// frame that comes here, with regions_body / every link by search and labels
+// re-read / now: random blocks of 1024x128 px with half of them linked 114 /
+// 120 / 92 us, a comb of those 103 / 101 / 86, a checkerboard of 240 x 135
+// blocks 74 / 69 / 57).  lds: gw * gh + 1 words.
 __device__ __forceinline__ void regions_loops(const FrameDesc& f, uint32_t* lds) {
     const int gw = f.gw, gh = f.gh, nb = gw * gh;
     const int t = threadIdx.x, lane = t & 63;
@@ -881,35 +884,72 @@ __device__ __forceinline__ void regions_loops(const FrameDesc& f, uint32_t* lds)
     const uint32_t gwm = gw > 1 ? (uint32_t)((0x100000000ull + (uint32_t)gw - 1) / (uint32_t)gw) : 0u;
     auto row_of = [&](int b) { return (int)div_u16((uint32_t)b, gwm, (uint32_t)gw); };
     if (t == 0) misc[0] = 0;
-    // kU blocks of each lane at a time, so that their loads are in flight
-    // together
-    constexpr int kU = 8, kStep = kU * kRegionThreads;
+    // kU blocks of each lane at a time, so that their reads are in flight
+    // together; bit i of a lane's masks is its block t + 1024 i
+    constexpr int kU = 8, kN = kRegionPer;
+    static_assert(kN == 32 && kN % kU == 0, "a bit a block of the lane");
     const int last = nb - 1;
-    // each block under the start of its run of the row in the wave's 64
-    // blocks, or under the block before them
-    for (int o = t; o - t < nb; o += kStep) {
+    auto block = [&](int i) { return t + i * kRegionThreads; };
+
+    // each block under the start of its run of the row (in a run longer than
+    // the wave's 64 blocks first under the block before them)
+    uint32_t runs_on = 0, solid = 0;  // the run starts before the wave's blocks; no edge block
+    for (int i = 0; i * kRegionThreads < nb; i += kU) {
         uint32_t s[kU], left[kU];
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
-            const int b = min(o + k * kRegionThreads, last);
+            const int b = min(block(i + k), last);
             s[k] = f.stats[b];
             left[k] = f.stats[max(b - 1, 0)];
         }
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
-            const int b = o + k * kRegionThreads;
+            const int b = block(i + k);
             const bool runs = b < nb && b != row_of(min(b, last)) * gw && linked(left[k], s[k], f.tau);
             const unsigned long long m = ~__ballot(runs) & (((1ull << lane) << 1) - 1ull);
-            if (b < nb) par[b] = (uint32_t)(m ? b - lane + 63 - __clzll((long long)m) : b - lane - 1);
+            if (b >= nb) continue;
+            par[b] = (uint32_t)(m ? b - lane + 63 - __clzll((long long)m) : b - lane - 1);
+            runs_on |= (uint32_t)!m << (i + k);
+            solid |= (uint32_t)!(s[k] >> 24) << (i + k);
         }
     }
     __syncthreads();
-    // links down, but for those that the blocks to the left have joined
-    for (int o = t; o + gw < nb; o += kStep) {
+    // the paths of the blocks in `which` down to their roots, by all lanes
+    // together: a block goes to where its parent points, and those above it
+    // take that step with it
+    auto shorten = [&](uint32_t which) {
+        for (int i = 0; i * kRegionThreads < nb; i += kU) {
+            if (!((which >> i) & 0xFFu)) continue;
+            uint32_t p[kU];
+#pragma unroll
+            for (int k = 0; k < kU; ++k) p[k] = lds_load(&par[min(block(i + k), last)]);
+            for (bool more = true; more;) {
+                uint32_t g[kU];
+#pragma unroll
+                for (int k = 0; k < kU; ++k) g[k] = lds_load(&par[p[k]]);
+                more = false;
+#pragma unroll
+                for (int k = 0; k < kU; ++k) {
+                    if (g[k] == p[k] || !((which >> (i + k)) & 1u)) continue;
+                    lds_store(&par[block(i + k)], g[k]);
+                    p[k] = g[k];
+                    more = true;
+                }
+            }
+        }
+    };
+    shorten(runs_on);
+    __syncthreads();
+
+    // links down, but for those that the blocks to the left have joined: the
+    // run below is hooked under the smallest run that it links to, by one
+    // atomic minimum a link
+    uint32_t down = 0;
+    for (int i = 0; i * kRegionThreads + gw < nb; i += kU) {
         uint32_t s[kU], left[kU], below[kU], bl[kU];
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
-            const int b = min(o + k * kRegionThreads, last - gw);
+            const int b = min(block(i + k), last - gw);
             const int l = max(b - 1, 0);
             s[k] = f.stats[b];
             left[k] = f.stats[l];
@@ -918,75 +958,136 @@ __device__ __forceinline__ void regions_loops(const FrameDesc& f, uint32_t* lds)
         }
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
-            const int b = o + k * kRegionThreads;
+            const int b = block(i + k);
             if (b + gw >= nb || !linked(s[k], below[k], f.tau)) continue;
-            if (b != row_of(b) * gw && linked(left[k], s[k], f.tau) && linked(bl[k], below[k], f.tau) &&
-                linked(left[k], bl[k], f.tau))
-                continue;
-            ufl_unite(par, (uint32_t)b, (uint32_t)(b + gw));
+            const bool row0 = b == row_of(b) * gw;
+            const bool above_runs = !row0 && linked(left[k], s[k], f.tau);
+            const bool below_runs = !row0 && linked(bl[k], below[k], f.tau);
+            if (above_runs && below_runs && linked(left[k], bl[k], f.tau)) continue;
+            // (only the words of run starts change here)
+            const uint32_t ra = above_runs ? par[b] : (uint32_t)b, rb = below_runs ? par[b + gw] : (uint32_t)(b + gw);
+            atomicMin(&par[rb], ra);
+            down |= 1u << (i + k);
         }
     }
     __syncthreads();
-    for (int b = t; b < nb; b += kRegionThreads) f.labels[b] = (int32_t)ufl_find(par, (uint32_t)b);
+    const uint32_t mine = t <= last ? 0xFFFFFFFFu >> (kN - 1 - (last - t) / kRegionThreads) : 0u;
+    shorten(mine);
+    __syncthreads();
+    // a run that links to several keeps the smallest: once more root under
+    // root for the links whose roots differ, then by search
+    for (int i = 0; i * kRegionThreads < nb; i += kU) {
+        if (!((down >> i) & 0xFFu)) continue;
+        uint32_t ra[kU], rb[kU];
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            ra[k] = lds_load(&par[min(block(i + k), last)]);
+            rb[k] = lds_load(&par[min(block(i + k) + gw, last)]);
+        }
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            if (!((down >> (i + k)) & 1u)) continue;
+            if (ra[k] == rb[k]) down &= ~(1u << (i + k));
+            else atomicMin(&par[max(ra[k], rb[k])], min(ra[k], rb[k]));
+        }
+    }
+    __syncthreads();
+    shorten(mine);
+    __syncthreads();
+    for (; down; down &= down - 1) {
+        const int b = block(__ffs(down) - 1);
+        if (lds_load(&par[b]) != lds_load(&par[b + gw])) ufl_unite(par, (uint32_t)b, (uint32_t)(b + gw));
+    }
+    __syncthreads();
+
+    // labels, kept in 16 bits a block
+    uint32_t root[kN / 2];
+#pragma unroll
+    for (int i = 0; i < kN; i += kU) {
+        if (i * kRegionThreads >= nb) break;
+        uint32_t p[kU];
+#pragma unroll
+        for (int k = 0; k < kU; ++k) p[k] = lds_load(&par[min(block(i + k), last)]);
+        for (bool more = true; more;) {
+            uint32_t g[kU];
+#pragma unroll
+            for (int k = 0; k < kU; ++k) g[k] = lds_load(&par[p[k]]);
+            more = false;
+#pragma unroll
+            for (int k = 0; k < kU; ++k) {
+                more |= g[k] != p[k];
+                p[k] = g[k];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            if (block(i + k) < nb) f.labels[block(i + k)] = (int32_t)p[k];
+            root[(i + k) / 2] = k & 1 ? root[(i + k) / 2] | (p[k] << 16) : p[k];
+        }
+    }
+    auto root_of = [&](int i) { return i & 1 ? root[i / 2] >> 16 : root[i / 2] & 0xFFFFu; };
     __syncthreads();
     for (int b = t; b < nb; b += kRegionThreads) par[b] = 0;
     __syncthreads();
     // per non-edge label the lowest row + 1 (low half), then the block count
     // (high half), by pieces of a row
-    for (int pass = 0; pass < 2; ++pass) {
-        for (int o = t; o - t < nb; o += kStep) {
-            uint32_t s[kU], root[kU];
+    uint32_t heads = 0;
 #pragma unroll
-            for (int k = 0; k < kU; ++k) {
-                const int b = o + k * kRegionThreads;
-                s[k] = b < nb ? f.stats[b] : 1u << 24;
-                root[k] = b < nb ? (uint32_t)f.labels[b] : 0xFFFFFFFFu;
-            }
-#pragma unroll
-            for (int k = 0; k < kU; ++k) {
-                const int b = min(o + k * kRegionThreads, last);
-                const bool ne = !(s[k] >> 24);
-                const int y = row_of(b);
-                const uint32_t left = (uint32_t)__shfl_up((int)root[k], 1);
-                const bool head = ne && (lane == 0 || b == y * gw || left != root[k]);
-                const unsigned long long stop = __ballot(head) | ~__ballot(ne);
-                if (head) {
-                    const unsigned long long m = lane < 63 ? stop >> (lane + 1) : 0ull;
-                    const uint32_t len = m ? (uint32_t)__ffsll((long long)m) : 64u - (uint32_t)lane;
-                    if (pass == 0) atomicMax(&par[root[k]], (uint32_t)y + 1u);
-                    else atomicAdd(&par[root[k]], len << 16);
-                }
-            }
+    for (int i = 0; i < kN; ++i) {
+        if (i * kRegionThreads >= nb) break;
+        const int b = min(block(i), last), y = row_of(b);
+        const uint32_t r = root_of(i), left = (uint32_t)__shfl_up((int)r, 1);
+        if (((solid >> i) & 1u) && (lane == 0 || b == y * gw || left != r)) {
+            atomicMax(&par[r], (uint32_t)y + 1u);
+            heads |= 1u << i;
         }
-        __syncthreads();
     }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kN; ++i) {
+        if (i * kRegionThreads >= nb) break;
+        const bool head = (heads >> i) & 1u;
+        const unsigned long long stop = __ballot(head) | ~__ballot((solid >> i) & 1u);
+        if (head) {
+            const unsigned long long m = lane < 63 ? stop >> (lane + 1) : 0ull;
+            atomicAdd(&par[root_of(i)], (m ? (uint32_t)__ffsll((long long)m) : 64u - (uint32_t)lane) << 16);
+        }
+    }
+    __syncthreads();
     // background = the largest non-edge component, ties to the smaller label;
     // each non-edge label's word becomes its depth
     uint32_t best = 0;
-    for (int b = t; b < nb; b += kRegionThreads) {
-        const uint32_t w = par[b];  // 0: not a non-edge label
-        if (!w) continue;
-        best = max(best, (w & 0xFFFF0000u) | (0xFFFFu - (uint32_t)b));
-        par[b] = (uint32_t)ramp((int)(w & 0xFFFFu) - 1, gh);
+    for (int i = 0; i * kRegionThreads < nb; i += kU) {
+        uint32_t w[kU];
+#pragma unroll
+        for (int k = 0; k < kU; ++k) w[k] = par[min(block(i + k), last)];
+#pragma unroll
+        for (int k = 0; k < kU; ++k) {
+            const int b = block(i + k);
+            if (b >= nb || !w[k]) continue;  // 0: not a non-edge label
+            best = max(best, (w[k] & 0xFFFF0000u) | (0xFFFFu - (uint32_t)b));
+            par[b] = (uint32_t)ramp((int)(w[k] & 0xFFFFu) - 1, gh);
+        }
     }
     best = wave_scan_max(best);
     if (lane == 63 && best) atomicMax(&misc[0], best);
     __syncthreads();
     const uint32_t bg = 0xFFFFu - (misc[0] & 0xFFFFu);
-    for (int o = t; o < nb; o += kStep) {
-        uint32_t s[kU], root[kU];
+#pragma unroll
+    for (int i = 0; i < kN; i += kU) {
+        if (i * kRegionThreads >= nb) break;
+        uint32_t s[kU], dep[kU];
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
-            const int b = min(o + k * kRegionThreads, last);
-            s[k] = f.stats[b];
-            root[k] = (uint32_t)f.labels[b];
+            s[k] = f.stats[min(block(i + k), last)];
+            dep[k] = par[root_of(i + k)];
         }
 #pragma unroll
         for (int k = 0; k < kU; ++k) {
-            const int b = o + k * kRegionThreads;
+            const int b = block(i + k);
             if (b >= nb) break;
-            const uint32_t dep = !(s[k] >> 24) && root[k] != bg ? par[root[k]] : (uint32_t)ramp(row_of(b), gh);
-            f.binfo[b] = make_uint2(s[k], dep | kResolved);
+            if ((s[k] >> 24) || root_of(i + k) == bg) dep[k] = (uint32_t)ramp(row_of(b), gh);
+            f.binfo[b] = make_uint2(s[k], dep[k] | kResolved);
         }
     }
 }

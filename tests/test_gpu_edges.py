@@ -269,3 +269,55 @@ def test_grouping_many_joins_in_a_batch(ctx):
     pstereo_synthesize_batch(ctx.handle, make_jobs(frames, outs, [8] * len(frames)), len(frames), p)
     for x, o, g in zip(host, outs, grids):
         refs.assert_views(o, refs.views(("many joins", *g), x, 8, K=2), f"batch of many joins {g}")
+
+
+def _noise(gw, gh, K):
+    """Blocks of random colours of nearly one luma, about half of the
+    neighbours linked: components of every shape."""
+    rng = np.random.default_rng(gw + gh)
+    img = np.full((gh, gw, 3), 90, np.int32)
+    d = rng.integers(-20, 21, (gh, gw))
+    img[..., 0] += d
+    img[..., 1] -= d // 2
+    return np.kron(img.astype(np.uint8), np.ones((K, K, 1), np.uint8))
+
+
+@pytest.mark.parametrize("gw,gh", [(512, 64), (2040, 16), (1025, 31), (300, 109)])
+def test_grouping_random_blocks(oracle_mod, gw, gh):
+    """Random blocks whose components overflow the merge, which then groups
+    the whole frame: labels, region depths and raw depth."""
+    from paper_2009_09501_amd import Context, pstereo_debug_blocks
+    K, w, h = 2, 2 * gw, 2 * gh
+    host = _noise(gw, gh, K)
+    dev = torch.device("cuda:0")
+    ctx = Context(0, w, h)
+    try:
+        print(f"random blocks {gw}x{gh}", flush=True)
+        raw = torch.empty((h, w), dtype=torch.uint8, device=dev)
+        ctx.synthesize(torch.from_numpy(host).to(dev), max_disparity=2, block_size=K, cbf_radius=0, out_depth_raw=raw)
+        torch.cuda.synchronize()
+        ref = oracle_mod.synthesize(host, 2, K=K, r=0)
+        _, labels, dblk = pstereo_debug_blocks(ctx.handle)
+        assert np.array_equal(labels, ref.labels.reshape(gh, gw))
+        assert np.array_equal(dblk, ref.dblk.reshape(gh, gw))
+        assert np.array_equal(raw.cpu().numpy(), ref.D0)
+    finally:
+        ctx.close()
+
+
+def test_grouping_random_blocks_in_a_batch(ctx):
+    """The same in one batch, beside rows too wide for a strip (grouped whole
+    too), some of them linked from end to end."""
+    from paper_2009_09501_amd import pstereo_params_init
+    from paper_2009_09501_amd.pstereo import PSTEREO_SYNC, make_jobs, pstereo_synthesize_batch
+    grids = [("noise", 512, 64), ("noise", 2040, 16), ("noise", 2100, 15), ("comb", 2100, 15), ("noise", 4098, 1),
+             ("comb", 4098, 7), ("stripes", 1500, 20)]
+    host = [_noise(gw, gh, 2) if kind == "noise" else _comb(gw, gh, 2, 2 if kind == "comb" else gh + 1)
+            for kind, gw, gh in grids]
+    frames = [torch.from_numpy(x).to("cuda:0") for x in host]
+    outs = [[torch.zeros_like(f) for _ in range(3)] for f in frames]
+    print("batch of random blocks", flush=True)
+    p = pstereo_params_init(block_size=2, flags=PSTEREO_SYNC)
+    pstereo_synthesize_batch(ctx.handle, make_jobs(frames, outs, [8] * len(frames)), len(frames), p)
+    for x, o, g in zip(host, outs, grids):
+        refs.assert_views(o, refs.views(("random blocks", *g), x, 8, K=2), f"batch of random blocks {g}")
