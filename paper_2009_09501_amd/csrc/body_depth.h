@@ -875,7 +875,9 @@ __host__ __device__ constexpr size_t rg_merge_lds_words(int nb) {
 // frame that comes here, with regions_body / every link by search and labels
 // re-read / now: random blocks of 1024x128 px with half of them linked 114 /
 // 120 / 92 us, a comb of those 103 / 101 / 86, a checkerboard of 240 x 135
-// blocks 74 / 69 / 57).  lds: gw * gh + 1 words.
+// blocks 74 / 69 / 57).  lds: regions_loops_lds_words(gw * gh) words.
+__host__ __device__ constexpr size_t regions_loops_lds_words(int nb) { return (size_t)nb + 1; }
+
 __device__ __forceinline__ void regions_loops(const FrameDesc& f, uint32_t* lds) {
     const int gw = f.gw, gh = f.gh, nb = gw * gh;
     const int t = threadIdx.x, lane = t & 63;

@@ -121,9 +121,15 @@ static LaunchSpec bs_k(const FrameDesc& f) {
 LaunchSpec spec_blockstats(const FrameDesc& f) { return f.aligned ? bs_k<true>(f) : bs_k<false>(f); }
 
 size_t regions_lds_bytes(int nb) { return regions_lds_bytes_c(nb); }
-size_t merge_lds_bytes(int nb) {
-    return std::max(std::max(rg_merge_lds_words(nb), rg_small_lds_words()) * 4, regions_lds_bytes_c(nb));
+// What the merge kernels run on a grid of nb blocks: the merge or the loops it
+// falls back to, and in a batch a small grid's grouping.
+static constexpr size_t merge_lds_words(int nb) {
+    return std::max(std::max(rg_merge_lds_words(nb), regions_loops_lds_words(nb)), rg_small_lds_words());
 }
+size_t merge_lds_bytes(int nb) { return merge_lds_words(nb) * 4; }
+static_assert(merge_lds_words(PSTEREO_MAX_BLOCKS) * 4 < regions_lds_bytes_c(PSTEREO_MAX_BLOCKS) - 12 * 1024 &&
+                  merge_lds_words(PSTEREO_MAX_BLOCKS) * 4 <= kMaxLds,
+              "no room for tables that only regions_body has");
 
 LaunchSpec spec_regions(const FrameDesc& f) {
     if (f.gw * f.gh <= kSmallBlocks)

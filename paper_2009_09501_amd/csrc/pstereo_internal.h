@@ -121,7 +121,7 @@ inline hipError_t launch_timed(const LaunchSpec& ls, const FrameDesc& f, hipStre
     return hipExtLaunchKernel(ls.func, ls.grid, ls.block, args, ls.lds, s, start, stop, 0);
 }
 size_t regions_lds_bytes(int nb);
-size_t merge_lds_bytes(int nb);  // the merge's own, or its fallback's
+size_t merge_lds_bytes(int nb);  // the merge's, its fallback's or a small grid's, the largest
 // Store v to *p (system-scope release) once everything before it on s is done.
 hipError_t launch_signal(unsigned long long* p, unsigned long long v, hipStream_t s);
 // Concurrency probe of two idle streams: a bounded wait on wait_on for a
