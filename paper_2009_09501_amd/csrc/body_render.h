@@ -174,43 +174,28 @@ __device__ __forceinline__ void quad_depth_tab(const FrameDesc& f, int x0, int y
     for (int j = 0; j < 4; ++j) D[j] = best[j] >= kNoCandidate ? fallback : (best[j] & 255u);
 }
 
-// Raw depth of the four pixels of a quad for blocks of 2 px (the quad spans
-// two block columns): the same rule as quad_depth_tab, per pixel, from the
-// block table in global memory (frames of 2 px blocks hold at most 2^17
-// pixels, so this path is never the bulk of the work).
-__device__ __forceinline__ uint2 block_entry_global(const FrameDesc& f, int bx, int by) {
-    if (bx < 0 || bx >= f.gw || by < 0 || by >= f.gh) return make_uint2(1u << 24, 0u);
-    uint2 e = f.binfo[by * f.gw + bx];
-    e.y = block_depth(f, by, e);
-    return e;
-}
-
-__device__ __forceinline__ void quad_depth_k2(const FrameDesc& f, int x0, int yy, const uint32_t (&col)[4],
-                                              uint32_t (&D)[4]) {
+// The same for blocks of 2 px, of which a quad spans two.
+__device__ __forceinline__ void quad_depth_tab2(const FrameDesc& f, int x0, int yy, const uint2* tab, int bx_lo,
+                                                int by_lo, int bp, const uint32_t (&col)[4], uint32_t (&D)[4]) {
     const int by = yy >> 1;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int bx = (x0 + j) >> 1;
-        const uint2 own = block_entry_global(f, bx, by);
-        if (!(own.x >> 24)) {
-            D[j] = own.y;
-            continue;
-        }
-        // first strict minimum of the L1 colour distance over the non-edge
-        // blocks of the 3 x 3 neighbourhood, in raster order
-        int best = -1;
-        uint32_t bestd = 0, bestdep = 0;
+    for (int h = 0; h < 2; ++h) {
+        const uint2* at = tab + (__umul24(by - by_lo, bp) + ((x0 >> 1) + h - bx_lo));
+        const uint2 own = *at;
+        D[2 * h] = D[2 * h + 1] = own.y;
+        if (!(own.x >> 24)) continue;
+        uint32_t best[2] = {0xFFFFFFFFu, 0xFFFFFFFFu};
+#pragma unroll
         for (int k = 0; k < 9; ++k) {
-            const uint2 c = block_entry_global(f, bx + k % 3 - 1, by + k / 3 - 1);
-            if (c.x >> 24) continue;
-            const uint32_t d = __builtin_amdgcn_sad_u8(col[j], c.x, 0u);
-            if (best < 0 || d < bestd) {
-                best = k;
-                bestd = d;
-                bestdep = c.y;
-            }
+            const uint2 c = at[(k / 3 - 1) * bp + (k % 3 - 1)];
+            const uint32_t tag = c.y | ((uint32_t)k << 8);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) best[j] = min(best[j], __builtin_amdgcn_sad_hi_u8(col[2 * h + j], c.x, tag));
         }
-        D[j] = best >= 0 ? bestdep : (uint32_t)ramp(by, f.gh);
+        uint32_t fallback = 0;
+        if (max(best[0], best[1]) >= kNoCandidate) fallback = (uint32_t)ramp(by, f.gh);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) D[2 * h + j] = best[j] >= kNoCandidate ? fallback : (best[j] & 255u);
     }
 }
 
@@ -325,8 +310,9 @@ __device__ __forceinline__ void cbf_pair(const uint32_t (&yw)[2 * R + 1][CbfPair
     }
 }
 
-// A tile of 64 x TH px (TH a multiple of 16) on 256 lanes.
-template <int R, int TH = kTileH>
+// A tile of 64 x TH px (TH a multiple of 16) on 256 lanes; K2: of blocks of
+// 2 px.
+template <int R, int TH = kTileH, bool K2 = false>
 struct CbfTile {
     static constexpr int NT = 256;
     static_assert(16 * TH % NT == 0, "whole passes over the tile's quads");
@@ -335,9 +321,10 @@ struct CbfTile {
     // tY, tD: TR * kRowWords words each; wtab: NK * 512 u16 and its zero tail;
     // work: 16 TH u16, a quarter per wave; nwork: 4 words
     // block table of the tile, its halo and one ring of neighbours, uint2
-    // each: at most 12 blocks a row (16 entries, TH / 8 + 4 rows) for blocks
-    // of 8 px and more, 20 x (TH / 4 + 4) for 4 px
-    static constexpr int kBlkEntries = 20 * (TH / 4 + 4);
+    // each: at most 12 blocks a row (16 entries) by TH / 8 + 4 for blocks of
+    // 8 px and more, 20 by TH / 4 + 4 for 4 px, 38 by TH / 2 + 6 for 2 px
+    static constexpr int kBlkPitch = K2 ? 38 : 20;
+    static constexpr int kBlkEntries = kBlkPitch * (K2 ? TH / 2 + 6 : TH / 4 + 4);
     static constexpr int kTabOff = 2 * TR * kRowWords;
     static constexpr int kWorkOff = kTabOff + NK * 256 + kWtabTail;
     static constexpr int kBlkOff = (kWorkOff + 8 * TH + 4 + 1) & ~1;  // 8-byte aligned
@@ -346,9 +333,11 @@ struct CbfTile {
 };
 
 // What a filter launch has to provide for: plain (generated depth, blocks of
-// 8 px and more, no depth dumps -- nearly every call), blocks of 2 px (raw
-// depth looked up per pixel in global memory, no block table in LDS), or any
+// 8 px and more, no depth dumps -- nearly every call), blocks of 2 px, or any
 // other.  The plain form drops the options' tests: 3840x2160 22.9 -> 21.8 us.
+// Blocks of 2 px take a form of their own for their larger table (looked up in
+// global memory, with their slots, 128 frames of 512x256 px at radius 2 took
+// 422 us a batch and one 72; from the table 275 and 49).
 enum class CbfKind { kPlain, kBlocks2, kAny };
 
 // One 64 x TH tile (tile_x, tile_y) on 256 lanes t = 0..255 (four whole
@@ -358,7 +347,8 @@ template <int R, bool ALIGNED, CbfKind KIND = CbfKind::kAny, int TH = kTileH>
 __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int tile_y, int t, uint32_t* lds,
                                          bool active) {
     constexpr int S = 2 * R + 1;
-    using T = CbfTile<R, TH>;
+    constexpr bool K2 = KIND == CbfKind::kBlocks2, PLAIN = KIND == CbfKind::kPlain;
+    using T = CbfTile<R, TH, K2>;
     constexpr int NT = T::NT;
     constexpr int TR = T::TR;
     constexpr int NK = T::NK;
@@ -370,7 +360,6 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
     int* nwork = reinterpret_cast<int*>(work + 16 * TH);  // per wave
     uint2* btab = reinterpret_cast<uint2*>(lds + T::kBlkOff);
 
-    constexpr bool K2 = KIND == CbfKind::kBlocks2, PLAIN = KIND == CbfKind::kPlain;
     const uint8_t* depth_in = PLAIN ? nullptr : f.depth_in;
     uint8_t* out_df = PLAIN ? nullptr : f.out_df;
     uint8_t* out_d0 = PLAIN ? nullptr : f.out_d0;
@@ -385,12 +374,12 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
     const int ks = __builtin_ctz((unsigned)f.K);
     const int bx_lo = max(-1, ((tx0 - 4) >> ks) - 1);
     const int by_lo = max(-1, ((ty0 - R) >> ks) - 1), by_hi = min(f.gh, ((ty0 + TH - 1 + R) >> ks) + 1);
-    const bool wide = PLAIN || ks >= 3;
-    const int bp = wide ? 16 : 20;
-    const bool table = !K2 && !depth_in && active;
+    const bool wide = PLAIN || (!K2 && ks >= 3);
+    const int bp = wide ? 16 : T::kBlkPitch;
+    const bool table = !depth_in && active;
     const int nbt = bp * (by_hi - by_lo + 1);
     auto entry_pos = [&](int i, int& bx, int& by) {
-        const int r = wide ? i >> 4 : i / 20;
+        const int r = wide ? i >> 4 : i / T::kBlkPitch;
         by = by_lo + r;
         bx = bx_lo + (i - r * bp);
     };
@@ -403,11 +392,17 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
         const uint32_t d = !in || (e.x >> 24) ? kNoCandidate : block_depth(f, by, e);
         btab[i] = make_uint2(in ? e.x : 1u << 24, d);
     };
-    int bx0 = 0, by0 = 0;
-    uint2 e0 = make_uint2(0u, 0u);
+    // a lane's first entries, all of them for blocks of 2 px and 8 px and more
+    constexpr int NB = K2 ? (T::kBlkEntries + NT - 1) / NT : 1;
+    static_assert(16 * (TH / 8 + 4) <= NT, "one pass for blocks of 8 px and more");
+    int bx0[NB], by0[NB];
+    uint2 e0[NB];
     if (table) {
-        entry_pos(t, bx0, by0);
-        e0 = entry_load(bx0, by0);
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            entry_pos(t + NT * k, bx0[k], by0[k]);
+            e0[k] = entry_load(bx0[k], by0[k]);
+        }
     }
 
     // the frame loads of all of a lane's quads of the tile and its halo.
@@ -448,8 +443,10 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
     }
 
     if (table) {
-        if (t < nbt) entry_store(t, bx0, by0, e0);
-        if (!PLAIN)  // (at most 12 x 8 blocks of 8 px and more: one pass)
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+            if (t + NT * k < nbt) entry_store(t + NT * k, bx0[k], by0[k], e0[k]);
+        if (!PLAIN && !K2)
             for (int i = t + NT; i < nbt; i += NT) {
                 int bx, by;
                 entry_pos(i, bx, by);
@@ -468,10 +465,10 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
     };
 
     // a tile whose windows all lie in non-edge blocks of one region depth is
-    // that depth (blocks of 8 px and more: at most 10 x 6 blocks under the
+    // that depth (blocks of 8 px and more: at most 10 x 8 blocks under the
     // windows, one per lane in two steps)
     bool uniform = false;
-    if (!K2 && !depth_in && wide && !out_d0) {
+    if (!depth_in && wide && !out_d0) {
         const int cx = min((max(tx0 - R, 0) >> ks) + (t & 15), min(tx0 + kTileW - 1 + R, W - 1) >> ks) - bx_lo;
         const int b0 = max(ty0 - R, 0) >> ks, b1 = min(ty0 + TH - 1 + R, H - 1) >> ks;
         const uint32_t c = btab[((ty0 >> ks) - by_lo) * bp + (tx0 >> ks) - bx_lo].y;
@@ -512,7 +509,7 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
             for (int j = 0; j < 4; ++j) D[j] = (dq[k] >> (8 * j)) & 255u;
         } else {
             quad_colours(vq[k], col);
-            if (K2) quad_depth_k2(f, x0, yy, col, D);
+            if (K2) quad_depth_tab2(f, x0, yy, btab, bx_lo, by_lo, bp, col, D);
             else quad_depth_tab(f, x0, yy, ks, btab, bx_lo, by_lo, bp, col, D);
         }
         if (!ALIGNED) {
@@ -548,7 +545,7 @@ __device__ __forceinline__ void cbf_tile(const FrameDesc& f, int tile_x, int til
             // is not uniform and goes to the filter without the pixel test:
             // the block-row steps of the background ramp are most of these)
             uint32_t c = 0, bad = 1, sure = 0;
-            if (!K2 && !depth_in && wide) {
+            if (!depth_in && wide) {
                 const int bxa = max(x0 - R, 0) >> ks, bxb = min(x0 + 3 + R, W - 1) >> ks;
                 const int bya = max(y - R, 0) >> ks, byb = min(y + R, H - 1) >> ks;
                 const uint2 e00 = btab[16 * (bya - by_lo) + (bxa - bx_lo)], e01 = btab[16 * (bya - by_lo) + (bxb - bx_lo)];

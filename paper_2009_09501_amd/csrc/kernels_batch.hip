@@ -94,7 +94,8 @@ __device__ __noinline__ void task_cbf(const FrameDesc* fp, int k, int items, int
     const int item = 4 * k + g;
     const bool active = item < items;
     const int tx = active ? item % gx : 0, ty = active ? item / gx : 0;
-    if (f.K == 2) cbf_tile<R, true, CbfKind::kBlocks2>(f, tx, ty, t, lds + g * CbfTile<R>::kLdsWords, active);
+    if (f.K == 2)
+        cbf_tile<R, true, CbfKind::kBlocks2>(f, tx, ty, t, lds + g * CbfTile<R, kTileH, true>::kLdsWords, active);
     else cbf_tile<R, true>(f, tx, ty, t, lds + g * CbfTile<R>::kLdsWords, active);
 }
 
@@ -273,7 +274,7 @@ __global__ void __launch_bounds__(kRegionThreads) k_mf_merge(const FrameDesc* fr
 
 template <int R, CbfKind KIND, int TH>
 __global__ void __launch_bounds__(256) k_mf_cbf(const FrameDesc* frames, const int* first, int n) {
-    __shared__ uint32_t lds[CbfTile<R, TH>::kLdsWords];
+    __shared__ uint32_t lds[CbfTile<R, TH, KIND == CbfKind::kBlocks2>::kLdsWords];
     const int idx = xcd_tile(blockIdx.x, gridDim.x);
     const int fi = frame_of(first, n, idx);
     const FrameDesc f = frames[fi];

@@ -20,7 +20,7 @@ __device__ __forceinline__ void warp_start_mark(const FrameDesc& f) {
 
 template <int R, bool ALIGNED, CbfKind KIND, int TH>
 __global__ void __launch_bounds__(256) k_cbf(FrameDesc f) {
-    __shared__ uint32_t lds[CbfTile<R, TH>::kLdsWords];
+    __shared__ uint32_t lds[CbfTile<R, TH, KIND == CbfKind::kBlocks2>::kLdsWords];
     // the start mark of a pipelined call: this kernel runs only once all
     // earlier work on its stream is done (a system-scope store that a
     // stream's wait-value packet polls; it publishes no data)

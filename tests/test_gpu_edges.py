@@ -321,3 +321,52 @@ def test_grouping_random_blocks_in_a_batch(ctx):
     pstereo_synthesize_batch(ctx.handle, make_jobs(frames, outs, [8] * len(frames)), len(frames), p)
     for x, o, g in zip(host, outs, grids):
         refs.assert_views(o, refs.views(("random blocks", *g), x, 8, K=2), f"batch of random blocks {g}")
+
+
+@pytest.mark.parametrize("w,h,r", [(1, 1, 2), (3, 2, 1), (63, 17, 3), (65, 33, 2), (66, 15, 0), (130, 49, 3), (362, 361, 2),
+                                   (2, 3000, 3), (1500, 20, 1)])
+def test_filter_blocks_of_2px(ctx, oracle_mod, w, h, r):
+    """Blocks of 2 px, many of them edge blocks that take a neighbour's depth,
+    on grids cut by the tiles and the frame: raw and filtered depth, views."""
+    from paper_2009_09501_amd import pstereo_params_init, pstereo_synthesize
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(w + h + r)
+    host = synth.gen_frame(300 + w + h, w, h, 12, 2.0)
+    host = np.where(rng.random((h, w, 1)) < 0.1, rng.integers(0, 256, (h, w, 3)), host).astype(np.uint8)
+    f = torch.from_numpy(host).to(dev)
+    outs = [torch.empty_like(f) for _ in range(3)]
+    d0, df = (torch.empty((h, w), dtype=torch.uint8, device=dev) for _ in range(2))
+    B = min(9, w)
+    print(f"2 px blocks {w}x{h} r={r}", flush=True)
+    p = pstereo_params_init(max_disparity=B, block_size=2, cbf_radius=r, out_depth=df, out_depth_raw=d0)
+    p.stream = torch.cuda.current_stream().cuda_stream
+    pstereo_synthesize(ctx.handle, f, w, h, p, *outs)
+    torch.cuda.synchronize()
+    ref = oracle_mod.synthesize(host, B, K=2, r=r)
+    assert np.array_equal(d0.cpu().numpy(), ref.D0)
+    assert np.array_equal(df.cpu().numpy(), ref.Df)
+    refs.assert_views(outs, refs.views(("2px", w, h, r), host, B, K=2, r=r), f"2 px blocks {w}x{h} r={r}")
+
+
+@pytest.mark.parametrize("K,w,h,n,r", [(4, 724, 724, 30, 2), (4, 724, 724, 30, 3), (2, 512, 256, 132, 2),
+                                       (2, 360, 364, 150, 3)])
+def test_batch_of_many_small_blocks(K, w, h, n, r):
+    """Batches of small blocks with more than 8192 filter tiles of 32 rows (the
+    tallest tiles, whose block table needs a second pass for 4 px): one frame
+    into n outputs."""
+    from paper_2009_09501_amd import Context, pstereo_params_init
+    from paper_2009_09501_amd.pstereo import PSTEREO_SYNC, make_jobs, pstereo_synthesize_batch
+    assert n * ((w + 63) // 64) * ((h + 31) // 32) > 8192
+    host = synth.gen_frame(77 + K + r, w, h, 30, 4.0)
+    f = torch.from_numpy(host).to("cuda:0")
+    outs = [[torch.zeros_like(f) for _ in range(3)] for _ in range(n)]
+    print(f"batch of {n} frames {w}x{h} K={K} r={r}", flush=True)
+    c = Context(0, w, h)
+    try:
+        p = pstereo_params_init(block_size=K, cbf_radius=r, flags=PSTEREO_SYNC)
+        pstereo_synthesize_batch(c.handle, make_jobs([f] * n, outs, [10] * n), n, p)
+        refs.assert_views(outs[0], refs.views(("small blocks", K, w, h, r), host, 10, K=K, r=r), f"K={K} r={r}")
+        for o in outs[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(o, outs[0]))
+    finally:
+        c.close()
