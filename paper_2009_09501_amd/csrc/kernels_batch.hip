@@ -316,7 +316,7 @@ __global__ void __launch_bounds__(1024) k_mf_warp(const FrameDesc* frames, const
 // The block size is the batch's (2 or 4 px) or at least 8 px throughout.
 template <int R, int TH>
 static const void* mf_cbf_fn(int block_size) {
-    return block_size == 2   ? (const void*)&k_mf_cbf<R, CbfKind::kBlocks2, TH>
+    return block_size == 2   ? (const void*)&k_mf_cbf<R, CbfKind::kBlocks2, kCbfRows2>
            : block_size == 4 ? (const void*)&k_mf_cbf<R, CbfKind::kAny, TH>
                              : (const void*)&k_mf_cbf<R, CbfKind::kPlain, TH>;
 }

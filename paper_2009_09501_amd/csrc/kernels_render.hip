@@ -262,21 +262,16 @@ bool warp_shape_cap(int w, int cap, WarpShape* out) {
     return true;
 }
 
-// (an external depth map needs no block lookups, whatever the block size)
-static CbfKind cbf_kind(const FrameDesc& f) {
-    if (f.K == 2 && !f.depth_in) return CbfKind::kBlocks2;
-    return f.K >= 8 && !f.depth_in && !f.out_df && !f.out_d0 ? CbfKind::kPlain : CbfKind::kAny;
+template <int R, bool A, CbfKind KIND, int TH>
+static LaunchSpec cbf_launch(const FrameDesc& f) {
+    return {reinterpret_cast<const void*>(&k_cbf<R, A, KIND, TH>),
+            dim3((f.w + kTileW - 1) / kTileW, (f.h + TH - 1) / TH), dim3(256), 0};
 }
 
 template <int R, bool A, int TH>
 static LaunchSpec cbf_th(const FrameDesc& f) {
-    const void* fn;
-    switch (cbf_kind(f)) {
-        case CbfKind::kPlain: fn = reinterpret_cast<const void*>(&k_cbf<R, A, CbfKind::kPlain, TH>); break;
-        case CbfKind::kBlocks2: fn = reinterpret_cast<const void*>(&k_cbf<R, A, CbfKind::kBlocks2, TH>); break;
-        default: fn = reinterpret_cast<const void*>(&k_cbf<R, A, CbfKind::kAny, TH>); break;
-    }
-    return {fn, dim3((f.w + kTileW - 1) / kTileW, (f.h + TH - 1) / TH), dim3(256), 0};
+    return f.K >= 8 && !f.depth_in && !f.out_df && !f.out_d0 ? cbf_launch<R, A, CbfKind::kPlain, TH>(f)
+                                                             : cbf_launch<R, A, CbfKind::kAny, TH>(f);
 }
 
 // Tile height of a filter launch.  Up to about six 32-row tiles per CU (1536;
@@ -293,6 +288,8 @@ int cbf_tile_rows(long long tiles32) { return tiles32 <= kShortTiles ? 16 : tile
 
 template <int R, bool A>
 static LaunchSpec cbf_spec(const FrameDesc& f) {
+    // (an external depth map needs no blocks, whatever their size)
+    if (f.K == 2 && !f.depth_in) return cbf_launch<R, A, CbfKind::kBlocks2, kCbfRows2>(f);
     switch (cbf_tile_rows((long long)((f.w + kTileW - 1) / kTileW) * ((f.h + 31) / 32))) {
         case 16: return cbf_th<R, A, 16>(f);
         case 48: return cbf_th<R, A, 48>(f);

@@ -365,7 +365,7 @@ int batch_prepare_internal(pstereo_batch* b, const pstereo_job* jobs, int n, con
             (void)pstereo::batch_tasks(b->h_frames[i], 2, &items, &gx);
             tiles32 += items;
         }
-        pl.cbf_rows = pstereo::cbf_tile_rows(tiles32);
+        pl.cbf_rows = p.block_size == 2 ? pstereo::kCbfRows2 : pstereo::cbf_tile_rows(tiles32);
         for (int i = 0; i < n; ++i) {
             const FrameDesc& f = b->h_frames[i];
             int items, gx;

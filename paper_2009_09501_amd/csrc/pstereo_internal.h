@@ -90,6 +90,10 @@ LaunchSpec spec_rg_merge(const FrameDesc& f);
 LaunchSpec spec_rg_final(const FrameDesc& f);
 LaunchSpec spec_cbf(const FrameDesc& f);
 int cbf_tile_rows(long long tiles32);  // from the number of 64 x 32 tiles
+// Filter tile rows for blocks of 2 px, whatever the launch: 16 / 32 / 48 rows
+// take 281 / 276 / 275 us for a batch of 128 frames of 512x256 px at radius 2
+// (8192 tiles of 32 rows), 365 / 370 / 383 for 140 at radius 3.
+constexpr int kCbfRows2 = 16;
 LaunchSpec spec_warp(const FrameDesc& f, const WarpShape& ws);
 // Block-iterative inpainting: reset (before the warp), the sweeps in launches
 // of kInpaintSweeps, composition once launch `last` has filled nothing in its
