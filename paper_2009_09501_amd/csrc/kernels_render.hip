@@ -334,12 +334,16 @@ LaunchSpec spec_warp(const FrameDesc& f, const WarpShape& ws) {
     // row.  At 1920x1080 the scalar registers allow seven waves a SIMD where
     // the vector ones alone would allow eight: three workgroups a CU, and a
     // grid of four made the rest wait for a second round (768 workgroups 9.9
-    // us, 1024 11.1, 540 11.9)
+    // us, 1024 11.1, 540 11.9).  Of workgroups of one or two waves, four or two
+    // take the place of one of four (1x60000 65 -> 36 us, 100x20000 28 -> 17,
+    // 500x9000 19.6 -> 17.6); of three waves, more than one a SIMD do not all
+    // fit (690x12000 32 -> 40)
     int waves_simd = 8;
     for (int i = 0; i < kWarpFns; ++i)
         if (warp_fn(i >= 6, i % 6 < 2 ? 1 : i % 6 < 4 ? 2 : 4, i & 1) == fn)
             waves_simd = g_warp_waves[i].load(std::memory_order_relaxed);
-    const int by_regs = std::max(1, waves_simd / ((ws.threads / 64 + 3) / 4));
+    const int waves = ws.threads / 64;
+    const int by_regs = std::max(1, waves < 4 ? 4 / waves * waves_simd : waves_simd / ((waves + 3) / 4));
     const int by_lds = std::max(1, (int)(kMaxLds / std::max<size_t>(ws.lds_bytes, 1)));
     const int by_lanes = std::max(1, 2048 / ws.threads);
     const int resident = std::min(std::min(by_lds, by_lanes), by_regs) * 256;

@@ -370,3 +370,20 @@ def test_batch_of_many_small_blocks(K, w, h, n, r):
             assert all(torch.equal(a, b) for a, b in zip(o, outs[0]))
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("w,h", [(1, 9000), (3, 8000), (100, 7300), (258, 7200), (500, 3700), (516, 1900), (690, 2000)])
+def test_rows_beyond_the_warp_grid(w, h):
+    """Narrow frames with more rows than the warp runs workgroups of one, two
+    and three waves at a time."""
+    from paper_2009_09501_amd import Context
+    host = synth.gen_frame(w + h, w, h, 20, 4.0)
+    B = min(15, w)
+    print(f"narrow {w}x{h}", flush=True)
+    c = Context(0, w, h)
+    try:
+        outs = c.synthesize(torch.from_numpy(host).to("cuda:0"), max_disparity=B, cbf_radius=1)
+        torch.cuda.synchronize()
+        refs.assert_views(outs, refs.views(("narrow", w, h), host, B, r=1), f"narrow {w}x{h}")
+    finally:
+        c.close()
