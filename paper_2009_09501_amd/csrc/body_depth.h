@@ -643,8 +643,7 @@ __host__ __device__ constexpr size_t regions_lds_bytes_c(int nb) {
 // list parts per strip (no atomic counters, one round of loads before the
 // merge's second), counts by row pieces, scans inside the vector unit and the
 // joins hooked at once (1920x1080, between first and last in-kernel time
-// stamp): strips 7.1 -> 4.6 us, merge 6.7 -> 6.0; 640x360 8.5 -> 4.5 and
-// 4.2 -> 4.1.
+// stamp): strips 7.1 -> 4.6 us, merge 6.7 -> 6.0.
 
 constexpr int kStripLanes = 1024;
 constexpr int kStripBlocks = 2048;
@@ -1108,9 +1107,9 @@ __device__ __forceinline__ void rg_merge_body(const FrameDesc& f, uint32_t* lds)
     uint16_t* joins = reinterpret_cast<uint16_t*>(misc + 4);  // blocks that join the strip above theirs
 
     // A wave takes strips wave, wave + 16, ..., and the rows they start with in
-    // pieces of 64 columns (lane l knows the l-th: at most 4 strips x 9 pieces,
-    // or 1 x 32).  One round of loads brings the counts of all strips, the
-    // first 64 slots of the wave's strips and the join bits of its pieces.
+    // pieces of 64 columns (lane l knows the l-th of at most kMaxPieces).  One
+    // round of loads brings the counts of all strips, the first 64 slots of the
+    // wave's strips and the join bits of its pieces.
     const uint2 hd =
         lane < nstrip ? *reinterpret_cast<const uint2*>(f.rhdr + lane * kStripHdrWords) : make_uint2(0u, 0u);
     const uint32_t own = hd.x;

@@ -141,13 +141,37 @@ LaunchSpec spec_regions(const FrameDesc& f) {
 // workgroup), 0 when a row does not fit a strip or one workgroup groups the
 // whole grid.  Narrow grids take strips of six rows (unless that makes more
 // than kMaxStrips): the unions inside a strip walk its rows one after the
-// other, which joining more strips does not (80x45 blocks: 12-row strips
-// 27.5 us a frame, six 26.5, two 26.8).
-int strip_rows(int gw, int gh) {
+// other, which joining more strips does not.  Measured, strips of 2 / 4 / 6 /
+// 8 / 12 rows: 850x480 (107x60 blocks) 32.3 / 31.4 / 31.3 / 31.7 / 31.6 us a
+// frame, 720x576 (90x72) 29.0 / 28.4 / 28.3 / 28.4 / 28.6, 960x540 (120x68)
+// 29.2 / 28.4 / 28.7 / 29.1 / 28.8.
+static constexpr int strip_rows_of(int gw, int gh) {
     if (gw < 1 || gw > kStripBlocks || gw * gh <= kSmallBlocks) return 0;
     if (gw > kStripLanes) return 1;
     return std::min(kStripLanes / gw, std::max(6, (gh + kMaxStrips - 1) / kMaxStrips));
 }
+int strip_rows(int gw, int gh) { return strip_rows_of(gw, gh); }
+
+// Over every grid of up to PSTEREO_MAX_BLOCKS blocks that takes strips: what
+// the strips and the merge assume of them.  (For one row count, strips and
+// pieces grow with gh, so the grids just before the count changes are enough.)
+static constexpr bool strips_fit() {
+    for (int gw = 1; gw <= kStripBlocks; ++gw) {
+        const int top = PSTEREO_MAX_BLOCKS / gw;
+        for (int gh = std::min(top, 6 * kMaxStrips);; gh = std::min(top, (gh / kMaxStrips + 1) * kMaxStrips)) {
+            if (const int rows = strip_rows_of(gw, gh)) {
+                const int strips = (gh + rows - 1) / rows;
+                const int pieces = (strips + kStripWaves - 1) / kStripWaves * ((gw + 63) / 64);
+                if (strips > kMaxStrips || pieces > kMaxPieces || rows * gw > kStripBlocks || rows > kStripLanes) return false;
+            }
+            if (gh >= top) break;
+        }
+    }
+    return true;
+}
+static_assert(strips_fit(), "strips within the merge's tables, their pieces a lane each, entries within a slot's bits");
+static_assert(kMaxPieces <= 64 && kMaxStrips <= 64, "a lane a strip and a lane a piece");
+static_assert(kStripHdrWords >= kStripHdrBits + kStripBlocks / 32, "a join bit a column");
 
 int strip_lanes(int gw, int rows) { return std::min(kStripLanes, (gw * rows + 63) / 64 * 64); }
 

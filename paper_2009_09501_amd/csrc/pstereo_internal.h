@@ -81,8 +81,15 @@ LaunchSpec spec_regions(const FrameDesc& f);
 int strip_rows(int gw, int gh);
 int strip_lanes(int gw, int rows);
 constexpr int kRegionSlots = 4096;  // slots the merge holds in LDS
-constexpr int kSmallBlocks = 4096;  // blocks of a grid grouped whole on one workgroup (k_rg_small)
-constexpr int kMaxStrips = 64;      // a strip but the last holds more than 512 blocks
+// Blocks of a grid grouped whole on one workgroup (k_rg_small): four a lane,
+// whose 64-block words are a lane each of one wave.  (Eight a lane, two words:
+// 850x480, 6420 blocks, 33.6 us a frame where strips take 29.8.)
+constexpr int kSmallBlocks = 4096;
+constexpr int kMaxStrips = 64;
+// 64-column pieces of the rows that one of the merge's 16 waves' strips start
+// with, a lane each: at most 62, for 17 one-row strips of 1921 to 1927 columns
+// (two strips of 31 pieces; a wider row leaves 16 rows, one strip a wave).
+constexpr int kMaxPieces = 62;
 constexpr int kStripHdrBits = 2;    // header word of the first join bits (2048 columns: 64 words)
 constexpr int kStripHdrWords = 66;
 LaunchSpec spec_rg_strip(const FrameDesc& f);

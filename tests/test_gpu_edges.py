@@ -206,10 +206,11 @@ def _joins(gw, gh, K, tooth):
 
 
 @pytest.mark.parametrize("gw,gh,tooth", [(512, 64, 15), (340, 96, 15), (341, 96, 15), (1000, 32, 24), (2047, 16, 24),
-                                         (513, 63, 24)])
+                                         (513, 63, 24), (1927, 17, 24), (1921, 17, 24), (1928, 16, 24), (992, 33, 24)])
 def test_grouping_many_joins(oracle_mod, gw, gh, tooth):
     """Few components and up to 15,000 joins across the strips' boundaries
-    (one, two or three rows a strip): labels, region depths and raw depth."""
+    (one, two or three rows a strip, up to 62 pieces of joins a wave of the
+    merge): labels, region depths and raw depth."""
     from paper_2009_09501_amd import Context, pstereo_debug_blocks
     K, w, h = 2, 2 * gw, 2 * gh
     host = _joins(gw, gh, K, tooth)
