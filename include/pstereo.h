@@ -323,9 +323,10 @@ const char *pstereo_batch_last_error(const pstereo_batch *b);
  * object the context keeps.  Same requirements and results as
  * pstereo_batch_run (per-job max_disparity; p's other fields shared); the
  * form is the staged one with 512-lane row-warp workgroups of 4 rows and
- * 64-row block-statistics tiles.  The first call, and any call with more jobs (above 64) or pixels (above one 4K
- * frame) than the context's batch object holds, synchronises the device and
- * allocates that object's scratch; later calls allocate nothing.  The call
+ * 32-row block-statistics tiles.  The first call, and any call with more jobs
+ * (above 64) or pixels (above one 4K frame) than the context's batch object
+ * holds, synchronises the device and allocates that object's scratch; later
+ * calls allocate nothing.  The call
  * uploads its job tables from pinned staging on the stream, so it is not
  * meant for graph capture (use pstereo_batch_prepare + pstereo_batch_launch).
  * With PSTEREO_SYNC it waits for the stream.  Errors as for

@@ -613,11 +613,15 @@ int pstereo_synthesize_batch(pstereo_ctx* ctx, const pstereo_job* jobs, int n, c
             pstereo::ctx_set_error(ctx, "batch scratch allocation failed");
             return rc;
         }
-        // the staged form with 512-lane row workgroups of 4 rows and 64-row
-        // block-statistics tiles, the tuning the autotuner picks for the
-        // uneven 720p..8K mix (64 frames: 1640 us; 2 rows 1692, 256 lanes
-        // 1699, 1024 lanes 1788, tiles of 16 or 32 rows 1703 and 1678)
-        b->tune = {PSTEREO_BATCH_STAGED, 512, 4, 0, 64};
+        // the staged form with 512-lane row workgroups of 4 rows (the tuning
+        // the autotuner picks for the uneven 720p..8K mix: 64 frames 1640 us; 2
+        // rows 1692, 256 lanes 1699, 1024 lanes 1788) and 32-row
+        // block-statistics tiles.  Tiles of 16 / 32 / 64 rows, and the defaults
+        // (32 up to 16 px blocks, else 64): that mix 1631 / 1568 / 1567, 1604;
+        // 32 frames of it 1594 / 1556 / 1551, 1576; 8 smaller ones 179 / 178 /
+        // 179, 178; one frame of 1280x720 34.8 / 35.0 / 36.3, 35.0, of 640x360
+        // 28.3 / 28.6 / 29.8, 28.5
+        b->tune = {PSTEREO_BATCH_STAGED, 512, 4, 0, 32};
         *slot = b;
     }
     const int rc = pstereo_batch_run(b, jobs, n, p);
