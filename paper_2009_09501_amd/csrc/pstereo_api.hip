@@ -67,13 +67,13 @@ void block_scratch_carve(BlockScratch& b, uint8_t* mem) {
     b.rhdr = reinterpret_cast<uint32_t*>(mem + off[4]);
 }
 
-// Allocate and carve one set; the strip headers start at zero.
+// Allocate and carve one set.
 hipError_t block_scratch_alloc(BlockScratch& b) {
     uint8_t* mem = nullptr;
     hipError_t e = hipMalloc(&mem, block_scratch_bytes());
     if (e != hipSuccess) return e;
     block_scratch_carve(b, mem);
-    return hipMemset(b.rhdr, 0, kBlkTableBytes[kBlkTables - 1]);
+    return hipSuccess;
 }
 
 // One filtered-depth image, rounded up so that the second one stays aligned.
@@ -277,14 +277,6 @@ int pstereo_create(pstereo_ctx** out, int device, int max_w, int max_h) {
     c->max_w = max_w;
     c->max_h = max_h;
     hipError_t e = hipSetDevice(device);
-    // what the device still runs is waited for before the set-up and not only
-    // after it, where the last line waits for the little that the set-up itself
-    // launched: a first call that comes right after a wait that put the host to
-    // sleep finds the launches slow.  First calls on new contexts, wait last /
-    // first (medians over processes): eight frames in three pipelined stages at
-    // 3840x2160 779 / 617 us, a video's 16 frames at 1920x1080 893 / 494, a
-    // gather at 3840x2160 87 / 83.  (An error shows in the calls below.)
-    if (e == hipSuccess && hipDeviceSynchronize() != hipSuccess) (void)hipGetLastError();
     if (e == hipSuccess) e = pstereo::prepare_depth_kernels();
     if (e == hipSuccess) e = pstereo::prepare_render_kernels();
     if (e != hipSuccess) {
