@@ -409,12 +409,15 @@ int pstereo_server_create(int device, int64_t hbm_budget_bytes, int max_streams,
             server_free(s);
             return rc;
         }
-        // a lane's batches are small: few rows a workgroup, and 32-row
-        // block-statistics tiles whatever the block size (burst of 16 frames:
-        // 932 us; the batch object's defaults, 256 lanes, one row and 64-row
-        // tiles, 968)
+        // a lane's batches are small and run beside the other lanes': few rows
+        // a workgroup, workgroups of 256 lanes, and 32-row block-statistics
+        // tiles whatever the block size.  Bursts of 16 frames from 1080p to 8K
+        // / 32 of 1080p / 32 of 720p / 8 of 4K: 892 / 483 / 272 / 426 us; with
+        // 512 lanes 892 / 524 / 333 / 427; with the batch object's defaults,
+        // one row and 64-row tiles for large blocks, 945 / 487 / 322 / 426;
+        // bursts of small frames (320x180 and 640x360, 2 to 32) within 3 %
         if (ln.batch) {
-            const pstereo_batch_tuning tune = {PSTEREO_BATCH_STAGED, 512, 2, 0, 32};
+            const pstereo_batch_tuning tune = {PSTEREO_BATCH_STAGED, 256, 2, 0, 32};
             (void)pstereo_batch_set_tuning(ln.batch, &tune);
         }
     }
