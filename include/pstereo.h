@@ -263,6 +263,10 @@ int pstereo_synthesize_noalloc(int device, const uint8_t *frame, int w, int h, c
  * The caller then promises that each frame was complete on the stream (or on
  * the host) before the previous pstereo_video_frame call was made -- frames
  * are supplied one ahead, as a decoder does.
+ * A frame whose stream is being captured is recorded with its own pointers, as
+ * a pstereo_synthesize call is, and runs when the graph is replayed (on the
+ * video's stream, before pstereo_video_end); in a pipelined video it is
+ * recorded one stage after the other, and the frames around it stay pipelined.
  * Errors as for pstereo_synthesize; PSTEREO_E_UNSUPPORTED for the excluded
  * parameters.
  */

@@ -776,7 +776,10 @@ int pstereo_profile_collect(pstereo_ctx* c, double ms_sum[4], int* count, double
 // context's side stream, the filter and warp on the video's stream after the
 // depth map of the same frame, and frame n works in block-table set n % 2; its
 // depth map waits only for what the video's stream held before frame n - 1's
-// call, so it is built during frame n - 1's filter and warp.
+// call, so it is built during frame n - 1's filter and warp.  A frame whose
+// stream is being captured is recorded one stage after the other, with tables
+// of its own: its filter would store its mark at a replay only, for which the
+// next frame's depth map, not captured, would wait.
 struct pstereo_video {
     pstereo_ctx* ctx = nullptr;
     int w = 0, h = 0;
@@ -787,8 +790,15 @@ struct pstereo_video {
     // pipelined: frame numbers, [0] the last frame whose depth map is done,
     // [1] the last frame whose depth filter has started (both only grow)
     unsigned long long* d_sig = nullptr;
+    BlockScratch recorded;  // pipelined: tables of recorded frames
     long long count = 0;
 };
+
+static void video_free(pstereo_video* v) {
+    (void)hipFree(v->d_sig);
+    (void)hipFree(v->recorded.mem);
+    delete v;
+}
 
 int pstereo_video_begin(pstereo_ctx* c, int w, int h, const pstereo_params* p, pstereo_video** out) {
     if (!c) return PSTEREO_E_INVALID;
@@ -831,9 +841,9 @@ int pstereo_video_begin(pstereo_ctx* c, int w, int h, const pstereo_params* p, p
     hipError_t e = hipSetDevice(c->device);
     if (v->pipe && e == hipSuccess) ensure_overlap(c, v->stream, false);
     if (v->pipe && e == hipSuccess && (e = hipMalloc(&v->d_sig, 16)) == hipSuccess) e = hipMemset(v->d_sig, 0, 16);
+    if (v->pipe && e == hipSuccess) e = block_scratch_alloc(v->recorded);
     if (e != hipSuccess) {
-        (void)hipFree(v->d_sig);
-        delete v;
+        video_free(v);
         return fail(c, PSTEREO_E_DEVICE, "video setup: %s", hipGetErrorString(e));
     }
     *out = v;
@@ -854,13 +864,19 @@ int pstereo_video_frame(pstereo_video* v, const uint8_t* frame, uint8_t* out_l, 
     if (e != hipSuccess) return fail(c, PSTEREO_E_DEVICE, "hipSetDevice: %s", hipGetErrorString(e));
     c->pipe_valid = false;  // a later plain pipelined call waits for this frame
     const unsigned long long fn = (unsigned long long)v->count + 1;  // this frame's number
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (s) e = hipStreamIsCapturing(s, &cap);  // (the null stream is never captured)
+    if (e != hipSuccess) return fail(c, PSTEREO_E_DEVICE, "capture status: %s", hipGetErrorString(e));
+    const bool recorded = cap != hipStreamCaptureStatusNone, pipe = v->pipe && !recorded;
     if (v->pipe) {
-        const BlockScratch& bs = c->blk[v->count % 2];
+        const BlockScratch& bs = pipe ? c->blk[v->count % 2] : v->recorded;
         f.stats = bs.stats;
         f.binfo = bs.binfo;
         f.labels = bs.labels;
         f.rlist = bs.rlist;
         f.rhdr = bs.rhdr;
+    }
+    if (pipe) {
         f.sig = v->d_sig;
         f.sig_value = fn;
         f.mark = v->d_sig + 1;
@@ -879,11 +895,11 @@ int pstereo_video_frame(pstereo_video* v, const uint8_t* frame, uint8_t* out_l, 
     int nk;
     frame_specs(f, ws, ls, nk, &stage);
     for (int i = 0; i < nk && e == hipSuccess; ++i) {
-        if (v->pipe && stage[i] == 2) e = hipStreamWaitValue64(s, v->d_sig, fn, hipStreamWaitValueGte, ~0ull);
-        if (e == hipSuccess) e = pstereo::launch(ls[i], f, v->pipe && stage[i] <= 1 ? c->side : s);
+        if (pipe && stage[i] == 2) e = hipStreamWaitValue64(s, v->d_sig, fn, hipStreamWaitValueGte, ~0ull);
+        if (e == hipSuccess) e = pstereo::launch(ls[i], f, pipe && stage[i] <= 1 ? c->side : s);
     }
     if (e != hipSuccess) {
-        if (v->pipe) {
+        if (pipe) {
             // drained, so that the next frame starts the pipeline again and no
             // kernel of this one is still to store its number
             (void)hipStreamSynchronize(c->side);
@@ -894,8 +910,11 @@ int pstereo_video_frame(pstereo_video* v, const uint8_t* frame, uint8_t* out_l, 
         }
         return fail(c, PSTEREO_E_DEVICE, "video frame: %s", hipGetErrorString(e));
     }
-    v->pipe_started = v->pipe;
-    v->count++;
+    if (recorded) return PSTEREO_OK;  // (pstereo_debug_blocks keeps to frames that ran)
+    if (pipe) {
+        v->pipe_started = true;
+        v->count++;
+    }
     c->have_blocks = true;
     c->last_fd = f;
     c->blocks_final = f.rstrip == 0;
@@ -909,8 +928,7 @@ int pstereo_video_end(pstereo_video* v) {
     if (!v) return PSTEREO_OK;
     (void)hipSetDevice(v->ctx->device);
     (void)hipStreamSynchronize(v->stream);
-    (void)hipFree(v->d_sig);
-    delete v;
+    video_free(v);
     return PSTEREO_OK;
 }
 

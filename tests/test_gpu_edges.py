@@ -388,3 +388,54 @@ def test_rows_beyond_the_warp_grid(w, h):
         refs.assert_views(outs, refs.views(("narrow", w, h), host, B, r=1), f"narrow {w}x{h}")
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("pipelined", [False, True])
+@pytest.mark.parametrize("w,h", [(640, 360), (1280, 720), (333, 190)])
+def test_video_frame_in_a_capture(ctx, w, h, pipelined):
+    """A frame recorded into a graph in the middle of a video: it runs at each
+    replay, on what its buffer then holds, and the frames after it and between
+    the replays are as without it."""
+    from paper_2009_09501_amd import pstereo_params_init
+    from paper_2009_09501_amd.pstereo import (PSTEREO_PIPELINE, pstereo_video_begin, pstereo_video_end,
+                                              pstereo_video_frame)
+    dev = torch.device("cuda:0")
+    host = [synth.gen_frame(40 + i, w, h, 16, 4.0) for i in range(8)]
+    frames = [torch.from_numpy(x).to(dev) for x in host]
+    B = synth.default_disparity(w)
+    want = [[torch.from_numpy(a).to(dev) for a in refs.views(("captured video", w, h, i), x, B)] for i, x in enumerate(host)]
+    outs = [torch.zeros_like(frames[0]) for _ in range(3)]
+    rec_in, rec = frames[0].clone(), [torch.zeros_like(frames[0]) for _ in range(3)]
+    s = torch.cuda.Stream()
+    p = pstereo_params_init(max_disparity=B, flags=PSTEREO_PIPELINE if pipelined else 0, stream=s.cuda_stream)
+    torch.cuda.synchronize()
+    print(f"video {w}x{h} pipelined={pipelined}: a frame in a capture", flush=True)
+    v = pstereo_video_begin(ctx.handle, w, h, p)
+    g = torch.cuda.CUDAGraph()
+
+    def run(i):
+        pstereo_video_frame(v, frames[i], *outs, ctx=ctx.handle)
+        s.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outs, want[i])), f"frame {i}"
+
+    try:
+        for i in range(3):
+            run(i)
+        with torch.cuda.graph(g, stream=s):
+            pstereo_video_frame(v, rec_in, *rec, ctx=ctx.handle)
+        assert not any(bool(x.any()) for x in rec), "a recorded frame runs at the replay"
+        for i in range(3, 6):
+            run(i)
+        for i in (6, 2, 7):
+            with torch.cuda.stream(s):
+                rec_in.copy_(frames[i])
+                pstereo_video_frame(v, frames[1], *outs, ctx=ctx.handle)
+                g.replay()
+                pstereo_video_frame(v, frames[4], *outs, ctx=ctx.handle)
+            s.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(rec, want[i])), f"replay on frame {i}"
+            assert all(torch.equal(a, b) for a, b in zip(outs, want[4])), f"after the replay on frame {i}"
+            run(5)
+    finally:
+        torch.cuda.synchronize()
+        pstereo_video_end(v)
