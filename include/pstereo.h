@@ -343,8 +343,8 @@ int pstereo_synthesize_batch(pstereo_ctx *ctx, const pstereo_job *jobs, int n, c
 /*
  * Batch forms and their tuning.
  *  PSTEREO_BATCH_STAGED (default): one launch per stage over all frames of
- *    the batch (block statistics, region grouping with one workgroup per
- *    frame, depth filter, then one row-warp launch per distinct row shape);
+ *    the batch (block statistics, region grouping in one or two launches,
+ *    depth filter, then one row-warp launch per distinct row shape);
  *    kernel boundaries order the stages.
  *  PSTEREO_BATCH_FUSED: one persistent kernel: its workgroups claim tasks
  *    (per frame: block statistics, region grouping, depth filter, warp) in a

@@ -1,6 +1,6 @@
 // gfx950 kernels of the stereo rendering (one frame per launch): the depth
-// filter on 64 x 32 tiles and the per-row warp; the bodies live in
-// body_render.h.
+// filter on tiles of 64 x 16, 32 or 48 px and the per-row warp; the bodies live
+// in body_render.h.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

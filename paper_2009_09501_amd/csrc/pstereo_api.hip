@@ -770,7 +770,7 @@ int pstereo_profile_collect(pstereo_ctx* c, double ms_sum[4], int* count, double
 // are launched directly.  (Replayed graphs of the same kernels were slower on
 // both sides: updating their arguments and launching two graphs cost the host
 // 51.5 us a frame, launching the kernels 26, and a replayed graph ran 5 us
-// longer on the GPU; 1920x1080 pipelined, 16 frames: 750-860 us -> 363.)
+// longer on the GPU; 1920x1080 pipelined, 16 frames: 814 us -> 361.)
 //
 // Pipelined video (PSTEREO_PIPELINE at begin): the depth-map stages go on the
 // context's side stream, the filter and warp on the video's stream after the
@@ -813,12 +813,12 @@ int pstereo_video_begin(pstereo_ctx* c, int w, int h, const pstereo_params* p, p
         pp = *p;
     }
     if (pp.flags & (PSTEREO_DEPTH_EXTERNAL | PSTEREO_WARP_GATHER | PSTEREO_INPAINT_BLOCKS))
-        return fail(c, PSTEREO_E_UNSUPPORTED, "video replay generates the depth map and warps (no "
+        return fail(c, PSTEREO_E_UNSUPPORTED, "a video generates its depth maps and warps (no "
                                               "PSTEREO_DEPTH_EXTERNAL / PSTEREO_WARP_GATHER)");
     if (pp.out_depth || pp.out_depth_raw || pp.out_hsbs)
-        return fail(c, PSTEREO_E_UNSUPPORTED, "video replay takes no depth dumps");
+        return fail(c, PSTEREO_E_UNSUPPORTED, "a video takes no depth dumps");
     if (pp.flags & PSTEREO_PIPELINE_DEEP)
-        return fail(c, PSTEREO_E_UNSUPPORTED, "video replay pipelines two stages (PSTEREO_PIPELINE), not three");
+        return fail(c, PSTEREO_E_UNSUPPORTED, "a video pipelines two stages (PSTEREO_PIPELINE), not three");
     pstereo_video* v = new (std::nothrow) pstereo_video;
     if (!v) return fail(c, PSTEREO_E_NOMEM, "host allocation failed");
     v->ctx = c;
